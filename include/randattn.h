@@ -310,13 +310,17 @@ ra_status ra_decode_attention(ra_cache* cache, int32_t layer, const void* q,
  * of RA_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it runs on
  * until the process ends (its address is looked up once per device, at
  * ra_cache_create).  The call allocates nothing and calls no allocating
- * routine.  It needs (slots up to the highest active one) * Hkv * splits * G
- * * 130 * 4 bytes of that array when the launch has more than one split per
- * head (always for f32; see ra_attention_plan), and returns RA_ERR_CAPACITY,
+ * routine.  It counts (slots up to the highest active one) * Hkv * S * G * 130
+ * * 4 bytes of that array when S > 1 (always for f32), and returns
+ * RA_ERR_CAPACITY,
  * before any launch, when that exceeds RA_NOALLOC_SCRATCH_BYTES.  Every call
  * on one GPU shares the array, from any cache: calls that overlap on one GPU
  * (other streams, other threads) race on it and must be serialised by the
- * caller.  Nothing in the array needs to start at zero. */
+ * caller.  Nothing in the array needs to start at zero.  S: the work items
+ * per head of ra_attention_plan; where these are one wavefront each (bf16),
+ * ceil(keys / s) with s = ceil(keys / min(64, round(256 / heads))) rounded up
+ * to 32 (attn_split rounded up to 32 if set), heads = active sequences * Hkv:
+ * never fewer than the partials a launch of grouped items writes. */
 #define RA_NOALLOC_SCRATCH_BYTES (8u << 20)
 ra_status ra_decode_attention_noalloc(ra_cache* cache, int32_t layer, const void* q,
                                       const void* k_new, const void* v_new, void* out,

@@ -134,6 +134,24 @@ size_t drops_bytes(const ra_config& c) {
                                       256));
 }
 
+// Attention launch plan (plan_for): work items of split_keys keys, `waves`
+// wavefronts each; group_waves > 0: items of one wavefront, group_waves
+// consecutive items of a head to a workgroup.
+struct Plan {
+  int split_keys = 0, max_splits = 0, waves = 1, wide_regs = 0;
+  int group_waves = 0;
+  int short_runs = 0;   // every item is at most 64 keys: the latency build
+  // partial slots per head that the no-alloc entry point's limit counts (at
+  // least the workgroups of a head)
+  int partials = 0;
+
+  int launch_waves() const { return group_waves ? group_waves : waves; }
+  int launch_keys() const { return group_waves ? group_waves * split_keys : split_keys; }
+  int launch_splits() const {
+    return group_waves ? (max_splits + group_waves - 1) / group_waves : max_splits;
+  }
+};
+
 }  // namespace
 
 struct ra_cache {
@@ -161,7 +179,7 @@ struct ra_cache {
   int32_t* arrivals = nullptr;           // split arrival counters (bf16 attention)
   // graph mode (see ra_graph_mode): launches that depend on no host state
   bool graph = false;
-  int graph_split_keys = 0, graph_max_splits = 0, graph_waves = 0, graph_wide_regs = 0;
+  Plan graph_plan;
   int graph_candidates = 0;              // bound on any event's candidate slots
   void* scratch = nullptr;               // device address of the no-alloc partials
 
@@ -249,23 +267,62 @@ void mirror_plan(SeqMeta& M, int r, bool at_trigger) {
 // about 256 workgroups run, one per CU, and W is the largest of 12, 8, 4
 // that leaves each wavefront a long enough run of keys (12 or 8
 // wavefronts keep 3 or 2 per SIMD in flight; a short run per wavefront
-// costs more in prologue than the extra wavefronts gain).  With many more
+// costs more in prologue than the extra wavefronts gain).  Fewer than 512
+// keys per workgroup: see short_plan.  With many more
 // heads than CUs the workgroups run in several waves of dispatch, and 4
 // wavefronts built for one wavefront per SIMD (accumulators in the
 // accumulation registers) stream best; between 256 and 768 heads the 4-
 // wavefront build that fits three workgroups per CU keeps every head
 // resident at once.  fp32 (VALU): one wavefront per item, about 1024 items.
-struct Plan {
-  int split_keys, max_splits, waves, wide_regs;
-};
+
+// A launch too small for 512 keys per CU (bf16): its time is the latency of
+// one round of loads and, for heads on several workgroups, of the merge, so
+// every wavefront is a work item of its own, of 32 or 64 keys, all loaded at
+// once (attn_bf16_short_kernel); a workgroup's wavefronts merge in LDS.
+// Measured on 8 KV heads (microseconds per launch, one head group of 4):
+//   up to 512 keys, one workgroup per head, no merge through memory: 5.9 at
+//     200 keys (7.7 as two workgroups of 4 x 32 keys);
+//   4 x 32 keys while a head has at most 12 workgroups: 8.9 at 1,090 keys
+//     (4 x 64: 9.7, 8 x 32: 11.5);
+//   4 x 64 keys beyond: 10.1 at 3,136 keys (4 x 32: 12.3, 25 partials per
+//     head to merge; 8 x 32: 11.7);
+//   past one workgroup per CU, 8 x 64: 16.3 at 16 heads of 5,000 keys (4 x 64:
+//     18.4) and 17.9 at 64 heads of 2,000 (18.8).
+// One wavefront per workgroup with 64 to 128 keys, merged by single
+// wavefronts, took 22.7 (1,090 keys) and 31.4 (3,136).
+void short_plan(Plan& p, int keys_max, int heads) {
+  const auto groups = [&](int keys) { return (keys_max + keys - 1) / keys; };
+  const auto one_round = [&](int keys) { return groups(keys) * heads <= 256; };
+  p.short_runs = 1;
+  if (keys_max <= 256) {
+    p.group_waves = 4;
+    p.split_keys = 64;
+  } else if (keys_max <= 512) {
+    p.group_waves = 8;
+    p.split_keys = 64;
+  } else if (groups(128) <= 12 && one_round(128)) {
+    p.group_waves = 4;
+    p.split_keys = 32;
+  } else if (groups(256) <= ra::kMaxSplits && one_round(256)) {
+    p.group_waves = 4;
+    p.split_keys = 64;
+  } else {
+    // more keys per wavefront only where the partials' slots run out
+    const int keys = (keys_max + 8 * ra::kMaxSplits - 1) / (8 * ra::kMaxSplits);
+    p.group_waves = 8;
+    p.split_keys = std::max(64, static_cast<int>(round_up(keys, 32)));
+    p.short_runs = p.split_keys <= 64;
+  }
+}
 
 // The plan for `n_active` sequences whose longest cache, the new row
 // included, has keys_max keys.
 Plan plan_for(const ra_cache* c, int keys_max, int n_active) {
   const int heads = std::max(1, n_active * c->cfg.num_kv_heads);
-  Plan p{0, 0, 1, 0};
+  const bool bf16 = c->cfg.dtype == RA_BF16;
+  Plan p;
   int splits = 1;
-  if (c->cfg.dtype == RA_BF16) {
+  if (bf16) {
     if (heads >= 768) {
       p.waves = 4;
       p.wide_regs = 1;
@@ -286,13 +343,22 @@ Plan plan_for(const ra_cache* c, int keys_max, int n_active) {
                                  : static_cast<int>(round_up((keys_max + splits - 1) / splits, unit));
   sk = std::max<int>(sk, static_cast<int>(round_up((keys_max + ra::kMaxSplits - 1) / ra::kMaxSplits, unit)));
   p.split_keys = sk;
-  p.max_splits = (keys_max + sk - 1) / sk;
+  p.max_splits = p.partials = (keys_max + sk - 1) / sk;
+  if (bf16 && p.waves == 1) {
+    // items of one wavefront, several of a head to a workgroup
+    if (c->cfg.attn_split > 0) {
+      p.group_waves = 4;
+      p.short_runs = sk <= 64;
+    } else {
+      short_plan(p, keys_max, heads);
+      p.max_splits = (keys_max + p.split_keys - 1) / p.split_keys;
+    }
+  }
   return p;
 }
 
 Plan attention_plan(const ra_cache* c) {
-  if (c->graph)
-    return Plan{c->graph_split_keys, c->graph_max_splits, c->graph_waves, c->graph_wide_regs};
+  if (c->graph) return c->graph_plan;
   // sized by the longest cache of this step (cached rows + the new one), so
   // that while sequences are younger than their budget no wavefront or split
   // is planned over rows that do not exist yet
@@ -385,10 +451,11 @@ ra_status launch_decode(ra_cache* c, int32_t layer, const void* q, const void* k
   a.split_stride = split_stride;
   a.layer = layer;
   a.max_seqs = c->slot_hi;
-  a.split_keys = plan.split_keys;
-  a.max_splits = plan.max_splits;
+  a.split_keys = plan.launch_keys();
+  a.max_splits = plan.launch_splits();
   a.arrivals = c->arrivals;
-  a.waves = plan.waves;
+  a.waves = plan.launch_waves();
+  a.short_runs = plan.short_runs;
   a.wide_regs = plan.wide_regs;
   // fp32 heads of several splits: merged by their last split, which spares
   // a launch and its gap; in graph mode the launches follow each other with
@@ -746,16 +813,21 @@ ra_status ra_decode_attention_noalloc(ra_cache* c, int32_t layer, const void* q,
   const ra_status st = check_decode(c, layer, q, k_new, v_new, out);
   if (st != RA_OK) return st;
   if (!c->scratch) return RA_ERR_STATE;
-  // partial slots only for the splits this launch has, packed per head
+  // partial slots only for the splits this launch has, packed per head; the
+  // limit counts plan.partials of them, never fewer than the launch uses
   const Plan plan = attention_plan(c);
-  const size_t items = static_cast<size_t>(c->slot_hi) * c->cfg.num_kv_heads * plan.max_splits;
-  const size_t floats = items * c->G * ra::kHeadDim;
-  const bool partials = c->cfg.dtype == RA_F32 || plan.max_splits > 1;
-  if (partials && (floats + items * c->G * 2) * sizeof(float) > ra::kNoAllocScratchBytes)
+  const auto items = [&](int per_head) {
+    return static_cast<size_t>(c->slot_hi) * c->cfg.num_kv_heads * per_head * c->G;
+  };
+  const bool partials = c->cfg.dtype == RA_F32 || plan.partials > 1;
+  if (partials && items(plan.partials) * (ra::kHeadDim + 2) * sizeof(float) >
+                      ra::kNoAllocScratchBytes)
     return RA_ERR_CAPACITY;
+  const int stride = std::max(1, plan.launch_splits());
   float* ws = static_cast<float*>(c->scratch);
-  return launch_decode(c, layer, q, k_new, v_new, out, plan, ws, ws + floats,
-                       std::max(1, plan.max_splits), static_cast<hipStream_t>(stream));
+  return launch_decode(c, layer, q, k_new, v_new, out, plan, ws,
+                       ws + items(stride) * ra::kHeadDim, stride,
+                       static_cast<hipStream_t>(stream));
 }
 
 ra_status ra_end_step(ra_cache* c, void* stream, int32_t* n_evicted) {
@@ -840,11 +912,7 @@ ra_status ra_graph_mode(ra_cache* c, int32_t on, void* stream) {
     if (candidates > ra::kMaxCandidates) return RA_ERR_UNSUPPORTED;
     const ra_status fl = flush_pending(c, s);
     if (fl != RA_OK) return fl;
-    const Plan p = plan_for(c, cap_max, n_active);
-    c->graph_split_keys = p.split_keys;
-    c->graph_max_splits = p.max_splits;
-    c->graph_waves = p.waves;
-    c->graph_wide_regs = p.wide_regs;
+    c->graph_plan = plan_for(c, cap_max, n_active);
     c->graph_candidates = candidates;
     c->graph = true;
     return RA_OK;

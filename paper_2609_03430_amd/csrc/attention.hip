@@ -31,6 +31,7 @@
 // two shuffles of the row maximum.
 // fp32 path (VALU): lanes own keys for the scores and channels for P.V.
 #include <mutex>
+#include <type_traits>
 
 #include "ra_internal.h"
 
@@ -199,21 +200,38 @@ __device__ __forceinline__ float load_shared_level(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ void load_shared_level(const float* p, float& x, float& y) {
+  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+  x = __uint_as_float(static_cast<uint32_t>(v));
+  y = __uint_as_float(static_cast<uint32_t>(v >> 32));
+}
+
+// One softmax state of two channels: running max, sum and numerators.
+struct Partial {
+  float m, l, o0, o1;
+};
+
 // The split partials of one head merged by the last of its splits to finish
-// (outputs of element type E: bf16 bits or float).  Every split stores its partials with store_shared_level
-// and waits until they are written; then one thread counts the split on the
-// head's arrival counter.  The split that brings the count to nsplit reads
-// every split's partials with load_shared_level, merges them as
-// combine_kernel does and resets the counter for the next launch.  Nothing
-// waits on another workgroup: the other splits simply end.  Called by every
-// thread of the workgroup after its partials are stored; the head and its
-// split count are taken afresh from the grid position and the slot record
+// (outputs of element type E: bf16 bits or float).  Every split stores its
+// partials with store_shared_level and waits until they are written; then one
+// thread counts the split on the head's arrival counter.  The split that
+// brings the count to nsplit reads every split's partials with
+// load_shared_level, merges them and resets the counter for the next launch.
+// Nothing waits on another workgroup: the other splits simply end.  Called by
+// every thread of the workgroup after its partials are stored; the head and
+// its split count are taken afresh from the grid position and the slot record
 // (kept from before the key loop, they would take registers the loop needs).
-template <typename E>
+//
+// Bound by the latency of the shared level: a thread owns two channels of one
+// query, and its splits' numerators, maxima and sums come as batches of
+// 8-byte loads all in flight together (4 or 16 splits per round trip), merged
+// by the thread itself with no exchange.  Where the workgroup has more
+// threads than the head has channel pairs, the splits are dealt to `parts`
+// groups of threads, which merge in LDS in split order.
+template <typename E, int NT>
 __device__ void merge_if_last(const AttnLaunch& a, int G, int Hq, int Hkv) {
-  __shared__ float sm[kMaxSplits * kMaxGroup];   // split maxima, then weights
-  __shared__ float sl[kMaxSplits * kMaxGroup];   // split sums
-  __shared__ float inv_l[kMaxGroup];
+  __shared__ Partial s_part[NT];
   __shared__ int last;
   const int slot = blockIdx.z, g = blockIdx.y, head = slot * Hkv + g;
   const int nsplit = (a.meta[slot].len + 1 + a.split_keys - 1) / a.split_keys;
@@ -231,67 +249,72 @@ __device__ void merge_if_last(const AttnLaunch& a, int G, int Hq, int Hkv) {
   }
   __syncthreads();
   if (!last) return;
-  const int t = threadIdx.x, nt = blockDim.x;
+  const int t = threadIdx.x;
   const float* ml = a.ws_ml + static_cast<int64_t>(head) * a.split_stride * G * 2;
   const float* po = a.ws_o + static_cast<int64_t>(head) * a.split_stride * G * kHeadDim;
-  // up to four splits and two outputs per thread: the numerators are loaded
-  // together with the maxima and sums (one round trip to the shared level
-  // instead of two)
-  constexpr int kFastSplits = 4, kFastItems = 2;
-  const bool fast = nsplit <= kFastSplits && G * kHeadDim <= kFastItems * nt;
-  float pv[kFastItems][kFastSplits];
-  if (fast) {
-#pragma unroll
-    for (int j = 0; j < kFastItems; ++j) {
-      const int idx = t + j * nt;
-#pragma unroll
-      for (int s = 0; s < kFastSplits; ++s)
-        pv[j][s] = s < nsplit && idx < G * kHeadDim
-                       ? load_shared_level(po + (s * G) * kHeadDim + idx) : 0.f;
-    }
-  }
-  for (int i = t; i < nsplit * G; i += nt) {
-    sm[i] = load_shared_level(ml + 2 * i);
-    sl[i] = load_shared_level(ml + 2 * i + 1);
-  }
-  __syncthreads();
-  if (t < G) {
-    float mx = kNegInf;
-    for (int s = 0; s < nsplit; ++s) mx = fmaxf(mx, sm[s * G + t]);
-    float lsum = 0.f;
-    for (int s = 0; s < nsplit; ++s) {
-      const float wt = exp2f(sm[s * G + t] - mx);
-      sm[s * G + t] = wt;
-      lsum += wt * sl[s * G + t];
-    }
-    inv_l[t] = 1.f / lsum;
-  }
-  __syncthreads();
   E* out = static_cast<E*>(a.out) + (static_cast<int64_t>(slot) * Hq + g * G) * kHeadDim;
-  const auto put = [&](int idx, float o) {
-    if constexpr (sizeof(E) == 2) out[idx] = f32_to_bf16(o);
-    else out[idx] = o;
-  };
-  if (fast) {
+  const int pairs = G * (kHeadDim / 2);
+  const int parts = max(1, min(NT / pairs, (nsplit + 3) / 4));
+  const int per = (nsplit + parts - 1) / parts;
+  const auto gather_by = [&](auto batch, int item, int lo, int hi) {
+    constexpr int kBatch = decltype(batch)::value;
+    const int q = item / (kHeadDim / 2), c = 2 * (item % (kHeadDim / 2));
+    Partial p{kNegInf, 0.f, 0.f, 0.f};
+    for (int s0 = lo; s0 < hi; s0 += kBatch) {
+      float m[kBatch], l[kBatch], x[kBatch], y[kBatch];
 #pragma unroll
-    for (int j = 0; j < kFastItems; ++j) {
-      const int idx = t + j * nt;
-      if (idx >= G * kHeadDim) break;
-      const int q = idx / kHeadDim;
-      float o = 0.f;
+      for (int j = 0; j < kBatch; ++j) {
+        const int row = min(s0 + j, hi - 1) * G + q;
+        load_shared_level(ml + 2 * row, m[j], l[j]);
+        load_shared_level(po + row * kHeadDim + c, x[j], y[j]);
+      }
+      float mx = p.m;
 #pragma unroll
-      for (int s = 0; s < kFastSplits; ++s)
-        if (s < nsplit) o += pv[j][s] * sm[s * G + q];
-      put(idx, o * inv_l[q]);
+      for (int j = 0; j < kBatch; ++j) mx = fmaxf(mx, m[j]);
+      const float keep = exp2f(p.m - mx);
+      p.m = mx;
+      p.l *= keep;
+      p.o0 *= keep;
+      p.o1 *= keep;
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const float w = s0 + j < hi ? exp2f(m[j] - mx) : 0.f;
+        p.l += w * l[j];
+        p.o0 += w * x[j];
+        p.o1 += w * y[j];
+      }
     }
+    return p;
+  };
+  const auto gather = [&](int item, int lo, int hi) {
+    return hi - lo <= 4 ? gather_by(std::integral_constant<int, 4>{}, item, lo, hi)
+                        : gather_by(std::integral_constant<int, 16>{}, item, lo, hi);
+  };
+  const auto put = [&](int item, const Partial& p) {
+    const float inv = 1.f / p.l;
+    if constexpr (sizeof(E) == 2) {
+      *reinterpret_cast<uint32_t*>(out + 2 * item) =
+          f32_to_bf16(p.o0 * inv) | static_cast<uint32_t>(f32_to_bf16(p.o1 * inv)) << 16;
+    } else {
+      *reinterpret_cast<float2*>(out + 2 * item) = make_float2(p.o0 * inv, p.o1 * inv);
+    }
+  };
+  if (parts == 1) {
+    for (int item = t; item < pairs; item += NT) put(item, gather(item, 0, nsplit));
     return;
   }
-  for (int idx = t; idx < G * kHeadDim; idx += nt) {
-    const int q = idx / kHeadDim;
-    float o = 0.f;
-    for (int s = 0; s < nsplit; ++s)
-      o += load_shared_level(po + (s * G) * kHeadDim + idx) * sm[s * G + q];
-    put(idx, o * inv_l[q]);
+  const int part = t / pairs;
+  if (part < parts && part * per < nsplit)
+    s_part[t] = gather(t % pairs, part * per, min(part * per + per, nsplit));
+  __syncthreads();
+  if (t < pairs) {
+    Partial p = s_part[t];
+    for (int k = 1; k < parts && k * per < nsplit; ++k) {
+      const Partial r = s_part[k * pairs + t];
+      const float mx = fmaxf(p.m, r.m), wp = exp2f(p.m - mx), wr = exp2f(r.m - mx);
+      p = Partial{mx, p.l * wp + r.l * wr, p.o0 * wp + r.o0 * wr, p.o1 * wp + r.o1 * wr};
+    }
+    put(t, p);
   }
 }
 
@@ -413,6 +436,63 @@ __device__ __forceinline__ void compute_block(Softmax& st, const BlockRegs& b,
   }
 }
 
+// The W wavefronts of a work item merge their states in LDS; an item that is
+// a whole head writes the normalised output, another one its partial (merged
+// by the head's last item, or with FUSED false by combine_kernel).
+template <int W, bool FUSED>
+__device__ __forceinline__ void finish_item(const AttnLaunch& a, const Work& w, int wave,
+                                            int qi, int grp, const Softmax& st, int G, int Hq, int Hkv,
+                                            float (&s_m)[W][kMaxGroup],
+                                            float (&s_l)[W][kMaxGroup],
+                                            float (&s_o)[W][kMaxGroup][kHeadDim]) {
+  const int head = w.slot * Hkv + w.g;
+  const int64_t item = static_cast<int64_t>(head) * a.split_stride + w.split;
+  uint16_t* out = static_cast<uint16_t*>(a.out);
+  // merge the W wavefronts in LDS
+  if (qi < G) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      *reinterpret_cast<f32x4*>(&s_o[wave][qi][16 * u + 4 * grp]) = st.acc[u];
+    if (grp == 0) {
+      s_m[wave][qi] = st.m;
+      s_l[wave][qi] = st.l;
+    }
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < G * kHeadDim; idx += 64 * W) {
+    const int q = idx / kHeadDim, c = idx % kHeadDim;
+    float mx = kNegInf;
+#pragma unroll
+    for (int v = 0; v < W; ++v) mx = fmaxf(mx, s_m[v][q]);
+    float lsum = 0.f, o = 0.f;
+#pragma unroll
+    for (int v = 0; v < W; ++v) {
+      const float sc = s_m[v][q] == kNegInf ? 0.f : exp2f(s_m[v][q] - mx);
+      lsum += s_l[v][q] * sc;
+      o += s_o[v][q][c] * sc;
+    }
+    if (w.nsplit == 1) {
+      out[(static_cast<int64_t>(w.slot) * Hq + w.g * G + q) * kHeadDim + c] =
+          f32_to_bf16(o / lsum);
+    } else if constexpr (FUSED) {
+      store_shared_level(a.ws_o + (item * G + q) * kHeadDim + c, o);
+      if (c == 0) {
+        store_shared_level(a.ws_ml + (item * G + q) * 2, mx);
+        store_shared_level(a.ws_ml + (item * G + q) * 2 + 1, lsum);
+      }
+    } else {
+      a.ws_o[(item * G + q) * kHeadDim + c] = o;
+      if (c == 0) {
+        a.ws_ml[(item * G + q) * 2] = mx;
+        a.ws_ml[(item * G + q) * 2 + 1] = lsum;
+      }
+    }
+  }
+  if constexpr (FUSED) {
+    if (w.nsplit > 1) merge_if_last<uint16_t, 64 * W>(a, G, Hq, Hkv);
+  }
+}
+
 // W wavefronts per workgroup share one (sequence, KV head, split) work item:
 // wavefront v takes the v-th W-th of the split's keys, and the wavefronts
 // merge their online-softmax states in LDS at the end.  When the
@@ -430,7 +510,7 @@ __global__ __launch_bounds__(64 * W, MINW) void attn_bf16_kernel(
   constexpr bool kFusedMerge = W != 12 || PAGED;
   __shared__ float s_m[W][kMaxGroup];
   __shared__ float s_l[W][kMaxGroup];
-  __shared__ float s_o[W > 1 ? W : 1][kMaxGroup][kHeadDim];
+  __shared__ float s_o[W][kMaxGroup][kHeadDim];
   const Work w = locate(a.meta, a.layer, Hkv, a.split_keys, pg);
   if (!w.valid) return;
   const int wave = threadIdx.x >> 6;
@@ -563,76 +643,120 @@ __global__ __launch_bounds__(64 * W, MINW) void attn_bf16_kernel(
                          static_cast<uint16_t*>(a.kpool),
                          static_cast<uint16_t*>(a.vpool), a.pos);
 
-  const int head = w.slot * Hkv + w.g;
-  const int64_t item = static_cast<int64_t>(head) * a.split_stride + w.split;
-  uint16_t* out = static_cast<uint16_t*>(a.out);
-  if constexpr (W == 1) {
-    if (qi < G) {
-      if (w.nsplit == 1) {
-        const float inv = 1.f / st.l;
-        const int64_t orow = (static_cast<int64_t>(w.slot) * Hq + w.g * G + qi) * kHeadDim;
+  finish_item<W, kFusedMerge>(a, w, wave, qi, grp, st, G, Hq, Hkv, s_m, s_l, s_o);
+}
+
+// A block of 32 rows for the short build, rows at or past len included: row
+// len is the step's new pair, rows past it are read from some cached row and
+// masked by the caller (keys) or replaced by zero in patch_values.  Every
+// lane issues the same sixteen loads whatever the block holds.
+__device__ __forceinline__ void load_block_any(BlockRegs& b, const uint16_t* Kb,
+                                               const uint16_t* Vb, const uint16_t* kn, int kb,
+                                               int len, const LaneMap& lm) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+  for (int t = 0; t < 2; ++t) {
+    const uint16_t* row = (kb + lm.krow[t] < len ? Kb + lm.krow[t] * kHeadDim : kn) + lm.kcol;
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            out[orow + 16 * u + 4 * grp + i] = f32_to_bf16(st.acc[u][i] * inv);
-      } else {
-        float* po = a.ws_o + (item * G + qi) * kHeadDim;
+    for (int s = 0; s < 4; ++s) b.k[t][s] = ld16(row + 32 * s);
+  }
+  // an 8-row tile with no row below len reads the block's first tile instead
+  const uint16_t* vt = Vb + (kb + lm.vrow < len ? lm.vrow * kHeadDim : 0) + lm.vch * 8;
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+  for (int u = 0; u < 8; ++u) b.v[u] = ld16_stream(vt + 16 * 8 * u);
+}
+
+// The new value at row len, zeros above it (vn: the lane's channel of each
+// 16-channel tile).
+__device__ __forceinline__ void patch_values(BlockRegs& b, const uint16_t (&vn)[8], int kb,
+                                             int len, const LaneMap& lm) {
+  const int at = len - kb - lm.vrow;         // the new row within the lane's tile
+  if (at < 8) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) store_shared_level(po + 16 * u + 4 * grp + i, st.acc[u][i]);
-        if (grp == 0) {
-          store_shared_level(a.ws_ml + (item * G + qi) * 2, st.m);
-          store_shared_level(a.ws_ml + (item * G + qi) * 2 + 1, st.l);
-        }
-      }
-    }
-  } else {
-    // merge the W wavefronts in LDS
-    if (qi < G) {
+    for (int u = 0; u < 8; ++u) {
+      uint16_t e8[8];
+      __builtin_memcpy(e8, &b.v[u], 16);
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        *reinterpret_cast<f32x4*>(&s_o[wave][qi][16 * u + 4 * grp]) = st.acc[u];
-      if (grp == 0) {
-        s_m[wave][qi] = st.m;
-        s_l[wave][qi] = st.l;
-      }
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < G * kHeadDim; idx += 64 * W) {
-      const int q = idx / kHeadDim, c = idx % kHeadDim;
-      float mx = kNegInf;
-#pragma unroll
-      for (int v = 0; v < W; ++v) mx = fmaxf(mx, s_m[v][q]);
-      float lsum = 0.f, o = 0.f;
-#pragma unroll
-      for (int v = 0; v < W; ++v) {
-        const float sc = s_m[v][q] == kNegInf ? 0.f : exp2f(s_m[v][q] - mx);
-        lsum += s_l[v][q] * sc;
-        o += s_o[v][q][c] * sc;
-      }
-      if (w.nsplit == 1) {
-        out[(static_cast<int64_t>(w.slot) * Hq + w.g * G + q) * kHeadDim + c] =
-            f32_to_bf16(o / lsum);
-      } else if constexpr (kFusedMerge) {
-        store_shared_level(a.ws_o + (item * G + q) * kHeadDim + c, o);
-        if (c == 0) {
-          store_shared_level(a.ws_ml + (item * G + q) * 2, mx);
-          store_shared_level(a.ws_ml + (item * G + q) * 2 + 1, lsum);
-        }
-      } else {
-        a.ws_o[(item * G + q) * kHeadDim + c] = o;
-        if (c == 0) {
-          a.ws_ml[(item * G + q) * 2] = mx;
-          a.ws_ml[(item * G + q) * 2 + 1] = lsum;
-        }
-      }
+      for (int e = 0; e < 8; ++e) e8[e] = e < at ? e8[e] : e == at ? vn[u] : uint16_t(0);
+      __builtin_memcpy(&b.v[u], e8, 16);
     }
   }
-  if constexpr (kFusedMerge) {
-    if (w.nsplit > 1) merge_if_last<uint16_t>(a, G, Hq, Hkv);
+}
+
+// Decode attention where the launch is bound by latency, not by bytes: at
+// most 64 keys per wavefront (see plan_for).  A wavefront issues the loads of
+// all its keys, the step's new pair among them, before it uses any: one round
+// trip to memory, where the streaming build takes one for its full blocks and
+// another for the block of the new pair, and reads its last block again for
+// every prefetch that runs out of blocks.
+template <int W, bool PAGED>
+__global__ __launch_bounds__(64 * W, 1) void attn_bf16_short_kernel(
+    AttnLaunch a, Paging pg, int G, int Hq, int Hkv, float scale_log2) {
+  __shared__ float s_m[W][kMaxGroup];
+  __shared__ float s_l[W][kMaxGroup];
+  __shared__ float s_o[W][kMaxGroup][kHeadDim];
+  const Work w = locate(a.meta, a.layer, Hkv, a.split_keys, pg);
+  if (!w.valid) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, qi = lane & 15, grp = lane >> 4;
+  const LaneMap lm = lane_map();
+  const uint16_t* kpool = static_cast<const uint16_t*>(a.kpool);
+  const uint16_t* vpool = static_cast<const uint16_t*>(a.vpool);
+  const int64_t new_row = (static_cast<int64_t>(w.slot) * Hkv + w.g) * kHeadDim;
+  const uint16_t* kn = static_cast<const uint16_t*>(a.k_new) + new_row;
+  const uint16_t* vn = static_cast<const uint16_t*>(a.v_new) + new_row;
+  const int kpw = a.split_keys / W;            // 32 or 64
+  const int k0 = w.k0 + wave * kpw;
+  const int k1 = min(k0 + kpw, w.k1);
+  const bool has = k0 < k1, two = k0 + 32 < k1;
+  const bool owns_last = has && k1 == w.n_keys;
+  auto load = [&](BlockRegs& b, int kb) {
+    // the block's first row; a block that starts at row len holds no cached
+    // row and reads (and does not use) the pool's first rows
+    const int64_t br = kb < w.len ? pool_row<PAGED>(w.rm, kb) : 0;
+    load_block_any(b, kpool + br * kHeadDim, vpool + br * kHeadDim, kn, kb, w.len, lm);
+  };
+
+  Softmax st;
+  st.m = kNegInf;
+  st.l = 0.f;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) st.acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (has) {
+    bf16x8 qop[4];
+    const uint16_t* qrow = static_cast<const uint16_t*>(a.q) +
+        (static_cast<int64_t>(w.slot) * Hq + w.g * G + (qi < G ? qi : 0)) * kHeadDim + 8 * grp;
+    uint16_t vnew[8];
+    if (owns_last) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) vnew[u] = vn[16 * u + lm.vch];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const u32x4 z = {0u, 0u, 0u, 0u};
+      const u32x4 x = ld16(qrow + 32 * s);
+      qop[s] = as_bf16x8(qi < G ? x : z);
+    }
+    BlockRegs b0;
+    load(b0, k0);
+    if (two) {
+      BlockRegs b1;
+      load(b1, k0 + 32);
+      compute_block(st, b0, qop, scale_log2, 32);
+      if (owns_last) patch_values(b1, vnew, k0 + 32, w.len, lm);
+      compute_block(st, b1, qop, scale_log2, min(32, k1 - k0 - 32));
+    } else {
+      if (owns_last) patch_values(b0, vnew, k0, w.len, lm);
+      compute_block(st, b0, qop, scale_log2, k1 - k0);
+    }
+    st.l += __shfl_xor(st.l, 16, 64);
+    st.l += __shfl_xor(st.l, 32, 64);
   }
+  finish_item<W, true>(a, w, wave, qi, grp, st, G, Hq, Hkv, s_m, s_l, s_o);
+  if (owns_last)
+    append_row<uint16_t, PAGED>(w, a.meta, Hkv, static_cast<const uint16_t*>(a.k_new),
+                                static_cast<const uint16_t*>(a.v_new),
+                                static_cast<uint16_t*>(a.kpool),
+                                static_cast<uint16_t*>(a.vpool), a.pos);
 }
 
 // ---------------------------------------------------------------------------
@@ -1080,7 +1204,7 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(AttnLaunch a, Paging pg, i
       }
     }
   }
-  merge_if_last<float>(a, G, Hq, Hkv);
+  merge_if_last<float, 64>(a, G, Hq, Hkv);
 }
 
 template <int GT, bool PAGED>
@@ -1104,7 +1228,13 @@ hipError_t launch_attention_t(const Shape& sh, const AttnLaunch& a, hipStream_t 
     hipLaunchKernelGGL((attn_bf16_move_kernel<8>), mgrid, dim3(512), 0, s, a, sh.L, sh.G,
                        sh.Hq, sh.Hkv, scale_log2);
   } else if (sh.dtype == 1) {
-    if (a.waves == 12)
+    if (a.short_runs && a.waves == 4)
+      hipLaunchKernelGGL((attn_bf16_short_kernel<4, PAGED>), grid, dim3(256), 0, s, a, sh.pg,
+                         sh.G, sh.Hq, sh.Hkv, scale_log2);
+    else if (a.short_runs && a.waves == 8)
+      hipLaunchKernelGGL((attn_bf16_short_kernel<8, PAGED>), grid, dim3(512), 0, s, a, sh.pg,
+                         sh.G, sh.Hq, sh.Hkv, scale_log2);
+    else if (a.waves == 12)
       hipLaunchKernelGGL((attn_bf16_kernel<12, 1, PAGED>), grid, dim3(768), 0, s, a, sh.pg,
                          sh.G, sh.Hq, sh.Hkv, scale_log2);
     else if (a.waves == 8)
@@ -1115,9 +1245,6 @@ hipError_t launch_attention_t(const Shape& sh, const AttnLaunch& a, hipStream_t 
                          sh.G, sh.Hq, sh.Hkv, scale_log2);
     else if (a.waves == 4)
       hipLaunchKernelGGL((attn_bf16_kernel<4, 2, PAGED>), grid, dim3(256), 0, s, a, sh.pg,
-                         sh.G, sh.Hq, sh.Hkv, scale_log2);
-    else if (a.waves == 1)
-      hipLaunchKernelGGL((attn_bf16_kernel<1, 2, PAGED>), grid, dim3(64), 0, s, a, sh.pg,
                          sh.G, sh.Hq, sh.Hkv, scale_log2);
     else
       return hipErrorInvalidConfiguration;

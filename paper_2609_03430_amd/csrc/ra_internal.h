@@ -161,7 +161,8 @@ struct AttnLaunch {
   int max_seqs;
   int split_keys;
   int max_splits;
-  int waves;           // wavefronts per work item (bf16 path: 1, 4, 8 or 12)
+  int waves;           // wavefronts per workgroup (bf16 path: 4, 8 or 12)
+  int short_runs;      // bf16, 8 wavefronts of at most 64 keys: the latency build
   int wide_regs;       // bf16, 4 wavefronts: the build for one wavefront per SIMD
   // some sequence has a deferred row move (bf16, one split per head): the
   // launch runs the kernel that moves rows while it attends
