@@ -317,10 +317,10 @@ ra_status ra_decode_attention(ra_cache* cache, int32_t layer, const void* q,
  * on one GPU shares the array, from any cache: calls that overlap on one GPU
  * (other streams, other threads) race on it and must be serialised by the
  * caller.  Nothing in the array needs to start at zero.  S: the work items
- * per head of ra_attention_plan; where these are one wavefront each (bf16),
- * ceil(keys / s) with s = ceil(keys / min(64, round(256 / heads))) rounded up
- * to 32 (attn_split rounded up to 32 if set), heads = active sequences * Hkv:
- * never fewer than the partials a launch of grouped items writes. */
+ * per head of ra_attention_plan; where these are one wavefront each, ceil(keys
+ * / s) with s = ceil(keys / min(64, n)) rounded up to 32 (attn_split rounded up
+ * to 32 if set), n = round(256 / heads) for bf16 and ceil(1024 / heads) for f32,
+ * heads = active sequences * Hkv: never fewer than the partials of the launch. */
 #define RA_NOALLOC_SCRATCH_BYTES (8u << 20)
 ra_status ra_decode_attention_noalloc(ra_cache* cache, int32_t layer, const void* q,
                                       const void* k_new, const void* v_new, void* out,

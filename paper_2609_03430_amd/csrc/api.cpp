@@ -273,7 +273,7 @@ void mirror_plan(SeqMeta& M, int r, bool at_trigger) {
 // wavefronts built for one wavefront per SIMD (accumulators in the
 // accumulation registers) stream best; between 256 and 768 heads the 4-
 // wavefront build that fits three workgroups per CU keeps every head
-// resident at once.  fp32 (VALU): one wavefront per item, about 1024 items.
+// resident at once.  fp32: see plan_f32.
 
 // A launch too small for 512 keys per CU (bf16): its time is the latency of
 // one round of loads and, for heads on several workgroups, of the merge, so
@@ -315,6 +315,23 @@ void short_plan(Plan& p, int keys_max, int heads) {
   }
 }
 
+// fp32: four items of one wavefront to a workgroup, about 256 workgroups, but
+// no more than 1,024 keys in one: where the rows are many, a second workgroup
+// per CU keeps more loads in flight (64 heads of 9,000 keys: 117 us with
+// 1,024 keys, 133 with 2,048; 384 heads of 2,000: 139 and 180 with one
+// workgroup per head), where they are few it only adds partials to merge (64
+// heads of 2,900: 40 us with 1,024 keys, 49 with 256).  Eight wavefronts to a
+// workgroup measured within 5%, mostly slower.
+void plan_f32(Plan& p, int keys_max, int heads) {
+  const int splits = std::max(1, (256 + heads / 2) / heads);
+  int64_t keys = round_up((keys_max + splits - 1) / splits, 64);
+  if (heads < 768) keys = std::min<int64_t>(keys, 1024);
+  // never more partials than the no-alloc limit counts
+  keys = std::max(keys, round_up(p.split_keys, 64));
+  p.split_keys = static_cast<int>(keys / 4);
+  p.max_splits = (keys_max + p.split_keys - 1) / p.split_keys;
+}
+
 // The plan for `n_active` sequences whose longest cache, the new row
 // included, has keys_max keys.
 Plan plan_for(const ra_cache* c, int keys_max, int n_active) {
@@ -344,11 +361,12 @@ Plan plan_for(const ra_cache* c, int keys_max, int n_active) {
   sk = std::max<int>(sk, static_cast<int>(round_up((keys_max + ra::kMaxSplits - 1) / ra::kMaxSplits, unit)));
   p.split_keys = sk;
   p.max_splits = p.partials = (keys_max + sk - 1) / sk;
-  if (bf16 && p.waves == 1) {
+  if (p.waves == 1) {
     // items of one wavefront, several of a head to a workgroup
-    if (c->cfg.attn_split > 0) {
+    if (c->cfg.attn_split > 0 || !bf16) {
       p.group_waves = 4;
-      p.short_runs = sk <= 64;
+      p.short_runs = bf16 && sk <= 64;
+      if (c->cfg.attn_split == 0) plan_f32(p, keys_max, heads);
     } else {
       short_plan(p, keys_max, heads);
       p.max_splits = (keys_max + p.split_keys - 1) / p.split_keys;
@@ -457,11 +475,6 @@ ra_status launch_decode(ra_cache* c, int32_t layer, const void* q, const void* k
   a.waves = plan.launch_waves();
   a.short_runs = plan.short_runs;
   a.wide_regs = plan.wide_regs;
-  // fp32 heads of several splits: merged by their last split, which spares
-  // a launch and its gap; in graph mode the launches follow each other with
-  // no gap and the merge kernel (256 threads per head, against the 64 of a
-  // split) is the faster of the two
-  a.merge_kernel = c->graph ? 1 : 0;
   if (move) {
     a.move = 1;
     a.waves = 8;

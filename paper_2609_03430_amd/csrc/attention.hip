@@ -29,7 +29,8 @@
 // 8 softmax weights are exactly the 8 keys its P^T operand needs (tile t
 // row 4a+i holds key 8a+4t+i), so no data moves between lanes except the
 // two shuffles of the row maximum.
-// fp32 path (VALU): lanes own keys for the scores and channels for P.V.
+// fp32 path (MFMA, v_mfma_f32_16x16x4_f32): the same two products over
+// 16-key blocks, the softmax weights kept in fp32.
 #include <mutex>
 #include <type_traits>
 
@@ -43,18 +44,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kNegInf = -__builtin_huge_valf();
-
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
-}
-
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
   bf16x8 r;
@@ -124,9 +113,9 @@ __device__ __forceinline__ void append_row(const Work& w, const SeqMeta* meta,
   if (lane == 0) pos[row] = meta[w.slot].prompt_len + meta[w.slot].step;
 }
 
-// Merge the split partials of one (sequence, KV head) into the output: the
-// fp32 path (its kernel writes partials for every head) and the 12-wavefront
-// contiguous bf16 build (heads of one split write their output themselves).
+// Merge the split partials of one (sequence, KV head) into the output, for
+// the 12-wavefront contiguous bf16 build (heads of one split write their
+// output themselves).
 // One workgroup per head, launched after the attention kernel (the kernel
 // boundary makes every partial visible).  Partial layout:
 //   ws_o[((head * split_stride + split) * G + q) * 128 + c]  numerator / 2^m
@@ -439,7 +428,7 @@ __device__ __forceinline__ void compute_block(Softmax& st, const BlockRegs& b,
 // The W wavefronts of a work item merge their states in LDS; an item that is
 // a whole head writes the normalised output, another one its partial (merged
 // by the head's last item, or with FUSED false by combine_kernel).
-template <int W, bool FUSED>
+template <typename E, int W, bool FUSED>
 __device__ __forceinline__ void finish_item(const AttnLaunch& a, const Work& w, int wave,
                                             int qi, int grp, const Softmax& st, int G, int Hq, int Hkv,
                                             float (&s_m)[W][kMaxGroup],
@@ -447,7 +436,7 @@ __device__ __forceinline__ void finish_item(const AttnLaunch& a, const Work& w, 
                                             float (&s_o)[W][kMaxGroup][kHeadDim]) {
   const int head = w.slot * Hkv + w.g;
   const int64_t item = static_cast<int64_t>(head) * a.split_stride + w.split;
-  uint16_t* out = static_cast<uint16_t*>(a.out);
+  E* out = static_cast<E*>(a.out);
   // merge the W wavefronts in LDS
   if (qi < G) {
 #pragma unroll
@@ -472,8 +461,9 @@ __device__ __forceinline__ void finish_item(const AttnLaunch& a, const Work& w, 
       o += s_o[v][q][c] * sc;
     }
     if (w.nsplit == 1) {
-      out[(static_cast<int64_t>(w.slot) * Hq + w.g * G + q) * kHeadDim + c] =
-          f32_to_bf16(o / lsum);
+      const int64_t idx_out = (static_cast<int64_t>(w.slot) * Hq + w.g * G + q) * kHeadDim + c;
+      if constexpr (sizeof(E) == 2) out[idx_out] = f32_to_bf16(o / lsum);
+      else out[idx_out] = o / lsum;
     } else if constexpr (FUSED) {
       store_shared_level(a.ws_o + (item * G + q) * kHeadDim + c, o);
       if (c == 0) {
@@ -489,7 +479,7 @@ __device__ __forceinline__ void finish_item(const AttnLaunch& a, const Work& w, 
     }
   }
   if constexpr (FUSED) {
-    if (w.nsplit > 1) merge_if_last<uint16_t, 64 * W>(a, G, Hq, Hkv);
+    if (w.nsplit > 1) merge_if_last<E, 64 * W>(a, G, Hq, Hkv);
   }
 }
 
@@ -643,7 +633,7 @@ __global__ __launch_bounds__(64 * W, MINW) void attn_bf16_kernel(
                          static_cast<uint16_t*>(a.kpool),
                          static_cast<uint16_t*>(a.vpool), a.pos);
 
-  finish_item<W, kFusedMerge>(a, w, wave, qi, grp, st, G, Hq, Hkv, s_m, s_l, s_o);
+  finish_item<uint16_t, W, kFusedMerge>(a, w, wave, qi, grp, st, G, Hq, Hkv, s_m, s_l, s_o);
 }
 
 // A block of 32 rows for the short build, rows at or past len included: row
@@ -751,7 +741,7 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_short_kernel(
     st.l += __shfl_xor(st.l, 16, 64);
     st.l += __shfl_xor(st.l, 32, 64);
   }
-  finish_item<W, true>(a, w, wave, qi, grp, st, G, Hq, Hkv, s_m, s_l, s_o);
+  finish_item<uint16_t, W, true>(a, w, wave, qi, grp, st, G, Hq, Hkv, s_m, s_l, s_o);
   if (owns_last)
     append_row<uint16_t, PAGED>(w, a.meta, Hkv, static_cast<const uint16_t*>(a.k_new),
                                 static_cast<const uint16_t*>(a.v_new),
@@ -1038,180 +1028,185 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_move_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// fp32, VALU
+// fp32, MFMA
 // ---------------------------------------------------------------------------
 
-// GT: the group size when fixed at compile time (1, 2, 4, 8), 0 for any G.
-template <int GT, bool PAGED>
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnLaunch a, Paging pg, int G_rt,
-                                                      int Hq, int Hkv,
-                                                      float scale_log2) {
-  constexpr int kQ = GT > 0 ? GT : kMaxGroup;   // query slots in registers
-  const int G = GT > 0 ? GT : G_rt;
-  __shared__ float qs[kMaxGroup][kHeadDim];
-  __shared__ float ps[kMaxGroup][64];
-  const Work w = locate(a.meta, a.layer, Hkv, a.split_keys, pg);
-  if (!w.valid) return;
-  const int lane = threadIdx.x;
-  const float* kpool = static_cast<const float*>(a.kpool);
-  const float* vpool = static_cast<const float*>(a.vpool);
-  const float* kn = static_cast<const float*>(a.k_new) +
-                    (static_cast<int64_t>(w.slot) * Hkv + w.g) * kHeadDim;
-  const float* vn = static_cast<const float*>(a.v_new) +
-                    (static_cast<int64_t>(w.slot) * Hkv + w.g) * kHeadDim;
-  const float* qg = static_cast<const float*>(a.q) +
-                    (static_cast<int64_t>(w.slot) * Hq + w.g * G) * kHeadDim;
-  for (int i = lane; i < G * kHeadDim; i += 64) qs[i / kHeadDim][i % kHeadDim] = qg[i];
-  __syncthreads();
+// A block of 16 keys in the operand registers of v_mfma_f32_16x16x4_f32
+// (lane r = lane & 15, group = lane >> 4).
+struct BlockF32 {
+  f32x4 k[8];   // key row r, channels 16t + 4*group + [0, 4)
+  f32x4 v[8];   // channel 16u + r, rows 4*group + [0, 4)
+};
 
-  float m[kQ], l[kQ], acc[kQ][2];
+// The block whose `rows` first rows are cached (key rows at Kb, value tiles at
+// Vb).  Rows past them read the block's first row or tile instead, so that
+// every lane issues the same loads whatever the block holds.
+__device__ __forceinline__ void load_block(BlockF32& b, const float* Kb, const float* Vb,
+                                           int rows) {
+  const int r = threadIdx.x & 15, grp = (threadIdx.x & 63) >> 4, tile = 8 * (grp >> 1);
+  const int k = (r < rows ? r * kHeadDim : 0) + 4 * grp;
+  const int v = (tile < rows ? tile * kHeadDim : 0) + r * 8 + 4 * (grp & 1);
 #pragma unroll
-  for (int q = 0; q < kQ; ++q) {
-    m[q] = kNegInf;
-    l[q] = 0.f;
-    acc[q][0] = acc[q][1] = 0.f;
-  }
-  const float vn0 = vn[lane], vn1 = vn[lane + 64];
-  for (int kb = w.k0; kb < w.k1; kb += 64) {
-    // scores: lanes own keys
-    const int key = kb + lane;
-    const bool valid = key < w.k1;
-    const float* krow = key < w.len ? kpool + pool_row<PAGED>(w.rm, key) * kHeadDim : kn;
-    float s[kQ];
+  for (int t = 0; t < 8; ++t) b.k[t] = *reinterpret_cast<const f32x4*>(Kb + k + 16 * t);
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) s[q] = 0.f;
-    if (valid) {
-      for (int c = 0; c < kHeadDim; c += 4) {
-        const float4 kv = *reinterpret_cast<const float4*>(krow + c);
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) {
-          if (GT > 0 || q < G)
-            s[q] += kv.x * qs[q][c] + kv.y * qs[q][c + 1] + kv.z * qs[q][c + 2] +
-                    kv.w * qs[q][c + 3];
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) {
-      if (GT > 0 || q < G) {
-        const float x = valid ? s[q] * scale_log2 : kNegInf;
-        const float mn = fmaxf(m[q], wave_max(x));
-        const float alpha = exp2f(m[q] - mn);
-        const float p = exp2f(x - mn);
-        l[q] = l[q] * alpha + wave_sum(p);
-        acc[q][0] *= alpha;
-        acc[q][1] *= alpha;
-        m[q] = mn;
-        ps[q][lane] = p;
-      }
-    }
-    __syncthreads();
-    // P.V: lanes own channels lane and lane + 64; a value tile holds the 8
-    // keys of a channel in 32 contiguous bytes, so a lane reads 8 keys with
-    // two 16-byte loads and the wavefront's reads are contiguous.  The
-    // chunk's tiles are all issued before any is used.  Rows at or past len
-    // are selected, not multiplied: the new value at len, zero above it.
-    const int nk = min(64, w.k1 - kb);
-    const int ntile = (nk + 7) >> 3;
-    float vv[8][2][8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      if (t < ntile) {
-        const int kt = kb + 8 * t;
-        // a tile of 8 rows lies in one page; only tiles holding a row below
-        // len are read from the pool (the others hold the new value or zero)
-        const float* base = vpool + (kt < w.len ? pool_row<PAGED>(w.rm, kt) : 0) * kHeadDim;
-        const float4* s0 = reinterpret_cast<const float4*>(base + lane * 8);
-        const float4* s1 = reinterpret_cast<const float4*>(base + (lane + 64) * 8);
-        const float4 a0 = s0[0], a1 = s0[1], b0 = s1[0], b1 = s1[1];
-        const float ea[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-        const float eb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int kj = kt + e;
-          vv[t][0][e] = kj < w.len ? ea[e] : (kj == w.len ? vn0 : 0.f);
-          vv[t][1][e] = kj < w.len ? eb[e] : (kj == w.len ? vn1 : 0.f);
-        }
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      if (t < ntile) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-#pragma unroll
-          for (int q = 0; q < kQ; ++q) {
-            if (GT > 0 || q < G) {
-              const float p = ps[q][8 * t + e];
-              acc[q][0] += p * vv[t][0][e];
-              acc[q][1] += p * vv[t][1][e];
-            }
-          }
-        }
-      }
-    }
-    __syncthreads();
-  }
-
-  if (w.k1 == w.n_keys)
-    append_row<float, PAGED>(w, a.meta, Hkv, static_cast<const float*>(a.k_new),
-                      static_cast<const float*>(a.v_new),
-                      static_cast<float*>(a.kpool),
-                      static_cast<float*>(a.vpool), a.pos);
-
-  // one split: the normalised output; several: the partials, merged by the
-  // split that finishes last (merge_if_last) or, with merge_kernel, by the
-  // merge kernel launched next
-  const int head = w.slot * Hkv + w.g;
-  if (w.nsplit == 1) {
-    float* out = static_cast<float*>(a.out) +
-                 (static_cast<int64_t>(w.slot) * Hq + w.g * G) * kHeadDim;
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) {
-      if (GT > 0 || q < G) {
-        const float inv = 1.f / l[q];
-        out[q * kHeadDim + lane] = acc[q][0] * inv;
-        out[q * kHeadDim + lane + 64] = acc[q][1] * inv;
-      }
-    }
-    return;
-  }
-  const int64_t item = static_cast<int64_t>(head) * a.split_stride + w.split;
-  if (a.merge_kernel) {
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) {
-      if (GT > 0 || q < G) {
-        float* po = a.ws_o + (item * G + q) * kHeadDim;
-        po[lane] = acc[q][0];
-        po[lane + 64] = acc[q][1];
-        if (lane == 0) {
-          a.ws_ml[(item * G + q) * 2] = m[q];
-          a.ws_ml[(item * G + q) * 2 + 1] = l[q];
-        }
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int q = 0; q < kQ; ++q) {
-    if (GT > 0 || q < G) {
-      float* po = a.ws_o + (item * G + q) * kHeadDim;
-      store_shared_level(po + lane, acc[q][0]);
-      store_shared_level(po + lane + 64, acc[q][1]);
-      if (lane == 0) {
-        store_shared_level(a.ws_ml + (item * G + q) * 2, m[q]);
-        store_shared_level(a.ws_ml + (item * G + q) * 2 + 1, l[q]);
-      }
-    }
-  }
-  merge_if_last<float, 64>(a, G, Hq, Hkv);
+  for (int u = 0; u < 8; ++u)
+    b.v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Vb + v + 16 * 8 * u));
 }
 
-template <int GT, bool PAGED>
-void launch_f32(const dim3& grid, hipStream_t s, const AttnLaunch& a, const Shape& sh,
-                float scale_log2) {
-  hipLaunchKernelGGL((attn_f32_kernel<GT, PAGED>), grid, dim3(64), 0, s, a, sh.pg, sh.G,
-                     sh.Hq, sh.Hkv, scale_log2);
+// One 16-key block at row kb.  S^T[key][query] = K . Q^T leaves each lane the
+// scores of keys 4*group + i of query r, which is the P^T operand of
+// O^T[channel][query] += V^T . P^T at key step i: no lane exchange but the
+// two shuffles of the row maximum.  Keys at `limit` and above are masked.
+__device__ __forceinline__ void compute_block(Softmax& st, const BlockF32& b,
+                                              const f32x4 (&qop)[8], float scale_log2,
+                                              int limit) {
+  // four accumulators: short sums (and independent products)
+  f32x4 sp[4] = {};
+#pragma unroll
+  for (int t = 0; t < 8; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      sp[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.k[t][i], qop[t][i], sp[i], 0, 0, 0);
+  float x[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    x[i] = ((sp[0][i] + sp[1][i]) + (sp[2][i] + sp[3][i])) * scale_log2;
+  if (limit < 16) {
+    const int grp = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (4 * grp + i >= limit) x[i] = kNegInf;
+  }
+  float bm = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+  bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
+  bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
+  const float mn = fmaxf(st.m, bm);
+  const float alpha = exp2f(st.m - mn);
+  float p[4], psum = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    p[i] = exp2f(x[i] - mn);
+    psum += p[i];
+  }
+  st.l = st.l * alpha + psum;
+  st.m = mn;
+  // the block's own sum first, then one addition per block: the running sum
+  // rounds once per 16 keys
+#pragma unroll
+  for (int u0 = 0; u0 < 8; u0 += 2) {
+    f32x4 o[2] = {};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        o[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.v[u0 + u][i], p[i], o[u], 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        st.acc[u0 + u][i] = fmaf(st.acc[u0 + u][i], alpha, o[u][i]);
+  }
+}
+
+// fp32 decode attention: a workgroup of four wavefronts per (sequence, KV
+// head, split), each streaming a quarter of the split's keys in 16-key blocks, two
+// blocks in flight.  Bound by HBM where the rows are many and by latency where
+// they are few; the group's queries are padded to 16, which the matrix cores
+// still do in a third of the time the rows take to arrive (64 products of 32
+// cycles per 16 KB block).  8 sequences of 8 heads, 2,900 rows: 40 us per
+// launch (4.7 TB/s) where single wavefronts on the vector ALU, one key per
+// lane, took 81 us (2.4 TB/s); 256 heads of 3,000 rows: 6.0 TB/s.
+template <bool PAGED>
+__global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnLaunch a, Paging pg, int G, int Hq,
+                                                          int Hkv, float scale_log2) {
+  constexpr int W = 4;
+  __shared__ float s_m[W][kMaxGroup];
+  __shared__ float s_l[W][kMaxGroup];
+  __shared__ float s_o[W][kMaxGroup][kHeadDim];
+  __shared__ __align__(16) float s_new[2][kHeadDim];   // the new pair, for its wavefront
+  const Work w = locate(a.meta, a.layer, Hkv, a.split_keys, pg);
+  if (!w.valid) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, qi = lane & 15, grp = lane >> 4;
+  const float* kpool = static_cast<const float*>(a.kpool);
+  const float* vpool = static_cast<const float*>(a.vpool);
+  const int64_t new_row = (static_cast<int64_t>(w.slot) * Hkv + w.g) * kHeadDim;
+  const int kpw = a.split_keys / W;            // a multiple of 16
+  const int k0 = __builtin_amdgcn_readfirstlane(w.k0 + wave * kpw);
+  const int k1 = min(k0 + kpw, w.k1);
+  const bool has = k0 < k1;
+  const bool owns_last = has && k1 == w.n_keys;
+  auto load = [&](BlockF32& b, int kb) {
+    // a block that starts at row len holds no cached row: it reads (and does
+    // not use) the block before it
+    const int64_t br = pool_row<PAGED>(w.rm, min(kb, max(0, w.len - 1) & ~15));
+    load_block(b, kpool + br * kHeadDim, vpool + br * kHeadDim, w.len - kb);
+  };
+
+  Softmax st;
+  st.m = kNegInf;
+  st.l = 0.f;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) st.acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (has) {
+    const float2 kn = reinterpret_cast<const float2*>(static_cast<const float*>(a.k_new) + new_row)[lane];
+    const float2 vn = reinterpret_cast<const float2*>(static_cast<const float*>(a.v_new) + new_row)[lane];
+    // Q^T operand: query qi, channels as the key rows' (zero past G)
+    f32x4 qop[8];
+    const float* qrow = static_cast<const float*>(a.q) +
+        (static_cast<int64_t>(w.slot) * Hq + w.g * G + (qi < G ? qi : 0)) * kHeadDim + 4 * grp;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(qrow + 16 * t);
+      qop[t] = qi < G ? x : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int last = (k1 - k0 - 1) / 16;       // blocks 0 .. last
+    BlockF32 b0, b1;
+    load(b0, k0);
+    load(b1, k0 + 16 * min(1, last));
+    if (owns_last) {
+      reinterpret_cast<float2*>(s_new[0])[lane] = kn;
+      reinterpret_cast<float2*>(s_new[1])[lane] = vn;
+    }
+    int i = 0;
+    for (; i + 1 < last; i += 2) {
+      // (the loads stay where they are: moved up among the products, they
+      // would need registers of their own)
+      compute_block(st, b0, qop, scale_log2, 16);
+      __builtin_amdgcn_sched_barrier(0);
+      load(b0, k0 + 16 * (i + 2));
+      __builtin_amdgcn_sched_barrier(0);
+      compute_block(st, b1, qop, scale_log2, 16);
+      __builtin_amdgcn_sched_barrier(0);
+      load(b1, k0 + 16 * min(i + 3, last));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (i < last) {
+      compute_block(st, b0, qop, scale_log2, 16);
+      b0 = b1;
+    }
+    if (owns_last) {
+      // row len takes the new pair, the values past it zero
+      const int at_row = w.len - (k0 + 16 * last), at = at_row - 4 * grp;
+      if (qi == at_row) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+          b0.k[t] = *reinterpret_cast<const f32x4*>(&s_new[0][16 * t + 4 * grp]);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b0.v[u][e] = e < at ? b0.v[u][e] : e == at ? s_new[1][16 * u + qi] : 0.f;
+    }
+    compute_block(st, b0, qop, scale_log2, k1 - (k0 + 16 * last));
+    st.l += __shfl_xor(st.l, 16, 64);
+    st.l += __shfl_xor(st.l, 32, 64);
+  }
+  finish_item<float, W, true>(a, w, wave, qi, grp, st, G, Hq, Hkv, s_m, s_l, s_o);
+  if (owns_last)
+    append_row<float, PAGED>(w, a.meta, Hkv, static_cast<const float*>(a.k_new),
+                             static_cast<const float*>(a.v_new), static_cast<float*>(a.kpool),
+                             static_cast<float*>(a.vpool), a.pos);
 }
 
 template <bool PAGED>
@@ -1254,16 +1249,9 @@ hipError_t launch_attention_t(const Shape& sh, const AttnLaunch& a, hipStream_t 
       hipLaunchKernelGGL(combine_kernel<uint16_t>, cgrid, dim3(256), 0, s, a, sh.G, sh.Hq,
                          sh.Hkv, true);
   } else {
-    switch (sh.G) {
-      case 1: launch_f32<1, PAGED>(grid, s, a, sh, scale_log2); break;
-      case 2: launch_f32<2, PAGED>(grid, s, a, sh, scale_log2); break;
-      case 4: launch_f32<4, PAGED>(grid, s, a, sh, scale_log2); break;
-      case 8: launch_f32<8, PAGED>(grid, s, a, sh, scale_log2); break;
-      default: launch_f32<0, PAGED>(grid, s, a, sh, scale_log2); break;
-    }
-    if (a.merge_kernel && a.max_splits > 1)
-      hipLaunchKernelGGL(combine_kernel<float>, cgrid, dim3(256), 0, s, a, sh.G, sh.Hq,
-                         sh.Hkv, true);
+    if (a.waves != 4) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(attn_f32_kernel<PAGED>, grid, dim3(256), 0, s, a, sh.pg, sh.G, sh.Hq,
+                       sh.Hkv, scale_log2);
   }
   return hipGetLastError();
 }
