@@ -425,6 +425,29 @@ ra_status flush_pending(ra_cache* c, hipStream_t s) {
   return RA_OK;
 }
 
+// An event of the due slots of [lo, hi), listed in `list` unless they are too
+// many; deferred: positions and drop lists only.  The moves of a listed event
+// may share the attention's split counters, idle and zero between steps.
+hipError_t launch_event(ra_cache* c, int lo, int hi, int candidates, bool deferred,
+                        const ra::DueList& list, hipStream_t s) {
+  ra::Shape sh = c->shape();
+  int32_t* drops = deferred ? c->drops : nullptr;
+  const int64_t heads = static_cast<int64_t>(c->cfg.num_layers) * c->cfg.num_kv_heads;
+  if (list.n && list.n * heads <= kMaxHeadsPerLaunch) {
+    sh.due = &list;
+    if (c->cfg.policy != RA_POLICY_EXTERNAL) {   // its rows pile up past evict_every
+      sh.move_sync = reinterpret_cast<uint32_t*>(c->arrivals);
+      sh.move_words = static_cast<int64_t>(c->cfg.max_seqs) * c->cfg.num_kv_heads;
+    }
+    return ra::launch_evict(sh, c->meta, c->kpool, c->vpool, c->pos, list.slot[0],
+                            list.slot[0] + 1, candidates, deferred, s, drops, c->cfg.evict_every);
+  }
+  return by_slot_chunks(c->cfg, lo, hi, [&](int a, int b) {
+    return ra::launch_evict(sh, c->meta, c->kpool, c->vpool, c->pos, a, b, candidates, deferred,
+                            s, drops, c->cfg.evict_every);
+  });
+}
+
 // Marks the layer appended and launches its append + attention with the
 // given partials buffers (split_stride partial slots per head).
 ra_status launch_decode(ra_cache* c, int32_t layer, const void* q, const void* k_new,
@@ -890,11 +913,12 @@ ra_status ra_end_step(ra_cache* c, void* stream, int32_t* n_evicted) {
     for (int i = c->slot_lo; i < c->slot_hi; ++i) n_active += c->mirror[i].active;
     const bool defer = c->drops && due == n_active && attention_plan(c).max_splits == 1;
     const int candidates = c->max_candidates_due();
-    RA_LAUNCH(by_slot_chunks(c->cfg, c->slot_lo, c->slot_hi, [&](int lo, int hi) {
-      return ra::launch_evict(c->shape(), c->meta, c->kpool, c->vpool, c->pos, lo, hi,
-                              candidates, defer, s, defer ? c->drops : nullptr,
-                              c->cfg.evict_every);
-    }));
+    ra::DueList list;
+    if (due <= ra::kDueList) {
+      for (int i = c->slot_lo; i < c->slot_hi; ++i)
+        if (c->mirror[i].active && c->mirror[i].due) list.slot[list.n++] = i;
+    }
+    RA_LAUNCH(launch_event(c, c->slot_lo, c->slot_hi, candidates, defer, list, s));
     if (defer) {
       RA_LAUNCH(ra::launch_mark_pending(c->meta, c->slot_lo, c->slot_hi, s));
       for (int i = c->slot_lo; i < c->slot_hi; ++i)
@@ -968,8 +992,9 @@ ra_status ra_evict_now(ra_cache* c, int32_t seq, void* stream) {
   mirror_plan(M, c->cfg.recent_r, true);
   if (M.due) {
     if (c->is_paged()) c->shrink(seq, M.len);
-    RA_LAUNCH(ra::launch_evict(c->shape(), c->meta, c->kpool, c->vpool, c->pos, seq,
-                               seq + 1, c->span(M), false, s));
+    ra::DueList list;
+    list.slot[list.n++] = seq;
+    RA_LAUNCH(launch_event(c, seq, seq + 1, c->span(M), false, list, s));
   }
   return RA_OK;
 }

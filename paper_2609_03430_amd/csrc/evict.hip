@@ -178,11 +178,17 @@ struct PagedRows {
 // returned and synchronises, then writes.  Sources are never below destinations and a
 // chunk's writes land below the next chunk's sources, so the move is
 // race-free.  Called by every thread of the workgroup.
-template <int NT, typename E, bool POS_ONLY, typename Rows, bool MOVE_POS = true>
+// `loaded` is called by every thread between a chunk's loads and its writes.
+struct NoHook {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <int NT, typename E, bool POS_ONLY, typename Rows, bool MOVE_POS = true,
+          typename Loaded = NoHook>
 __device__ __forceinline__ void compact_rows(const int* f, int m, int* src_of, int d0,
                                              int new_len, int old_len, const Rows& row,
                                              E* __restrict__ kpool, E* __restrict__ vpool,
-                                             int32_t* __restrict__ P) {
+                                             int32_t* __restrict__ P,
+                                             const Loaded& loaded = Loaded()) {
   constexpr bool PAGED = Rows::kPaged;
   constexpr int kEpu = 16 / sizeof(E);            // elements per 16-byte unit
   constexpr int kKUnitsRow = kHeadDim / kEpu;     // 16-byte units per key row
@@ -252,6 +258,7 @@ __device__ __forceinline__ void compact_rows(const int* f, int m, int* src_of, i
     // every load of this chunk has returned before any thread writes
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
+    loaded();
 
     if (pos_mine) P[row.pos_row(j0 + t)] = pval;
     if constexpr (!POS_ONLY) {
@@ -288,14 +295,15 @@ __global__ __launch_bounds__(NT) void evict_kernel(
     const SeqMeta* __restrict__ meta, E* __restrict__ kpool,
     E* __restrict__ vpool, int32_t* __restrict__ pos, int L, int Hkv, int r,
     int slot_lo, int policy, int block, Paging pg, int32_t* __restrict__ drops_out,
-    int drop_stride) {
+    int drop_stride, DueList due, bool lists_in_pos) {
   constexpr bool PAGED = LAYOUT == 2;
   static_assert(KPT <= 32, "drop flags live in one 32-bit mask");
   __shared__ SelectShared sel_sh;
   __shared__ int f[kMaxEvery];
 
   const int per_seq = L * Hkv;
-  const int slot = slot_lo + static_cast<int>(blockIdx.x) / per_seq;
+  const int at = static_cast<int>(blockIdx.x) / per_seq;
+  const int slot = due.n ? due.slot[at] : slot_lo + at;
   const int lg = static_cast<int>(blockIdx.x) % per_seq;
   const int layer = lg / Hkv, g = lg % Hkv;
   const SeqMeta& Mref = meta[slot];
@@ -473,6 +481,14 @@ __global__ __launch_bounds__(NT) void evict_kernel(
         compact_rows<NT, E, true>(f, m, src_of, new_len - r, new_len, old_len,
                                   RegionRows{region}, kpool, vpool, P);
     }
+    // the drop list for move_chunks_kernel, in the m rows that the compacted
+    // positions leave free (every read of these rows lies before a barrier)
+    if (lists_in_pos) {
+      for (int k = t; k < m; k += NT) {
+        if constexpr (PAGED) pos[prow(new_len + k)] = f[k] + k;
+        else P[new_len + k] = f[k] + k;
+      }
+    }
     return;
   }
   if constexpr (PAGED)
@@ -532,21 +548,118 @@ __global__ __launch_bounds__(NT) void move_pending_kernel(
                                                 RegionRows{region}, kpool, vpool, nullptr);
 }
 
+// The moves of an event whose due heads are fewer than the CUs, after a
+// positions-only selection that left each head's drop list in its rows of
+// positions past the new length.  Every chunk of chunk_rows destination rows
+// gets a workgroup of its own (grid: n_chunks per head of the listed slots),
+// which loads its source rows, says so, and writes once the workgroup of the
+// chunk before has loaded its own.  Rows move down by less than a chunk, so
+// those sources reach into this chunk, and no other chunk's do.  A head's workgroups
+// take their chunks in the order in which they start, so the one waited for
+// is always running or done, and it waits for nothing before it says so:
+// every wait ends.  A head's sync word counts the chunks taken (bits 0-4) and
+// the workgroups done (5-9) and has a bit per chunk loaded (10-30); the last
+// workgroup done clears it.
+//
+// One workgroup moves a head at 22 GB/s each way however idle the chip: an
+// event of 20 heads of 9,300 rows took 243 us on 20 CUs.  With a workgroup per
+// 512 rows it takes 24 us for the selection and 55 for the moves (3.5 TB/s of
+// reads and writes; 28 us for 10 heads); 64 paged heads of 3,100 rows: 12 + 53
+// us, 86 before.
+constexpr int kMaxChunks = 21;
+struct ChunkLoaded {
+  uint32_t* word;
+  int chunk;
+  // called once, when every load of the workgroup has returned
+  __device__ __forceinline__ void operator()() const {
+    if (threadIdx.x == 0) {
+      __hip_atomic_fetch_or(word, 1024u << chunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (chunk > 0) {
+        while (!(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
+                 (512u << chunk)))
+          __builtin_amdgcn_s_sleep(2);
+      }
+    }
+    __syncthreads();
+  }
+};
+template <int NT, typename E, bool PAGED>
+__global__ __launch_bounds__(NT) void move_chunks_kernel(
+    const SeqMeta* __restrict__ meta, E* __restrict__ kpool, E* __restrict__ vpool,
+    const int32_t* __restrict__ pos, int L, int Hkv, int n_chunks, DueList due, Paging pg,
+    uint32_t* __restrict__ sync_words) {
+  constexpr int kChunk = chunk_rows<NT, E>();
+  __shared__ int f[kMaxEvery];
+  __shared__ int src_of[kChunk];
+  __shared__ int tbl[PAGED ? kMaxPagesLds : 1];
+  __shared__ int s_chunk;
+  const int per_seq = L * Hkv;
+  const int head = static_cast<int>(blockIdx.x) / n_chunks;
+  const int slot = due.slot[head / per_seq];
+  const int lg = head % per_seq;
+  const SeqMeta& M = meta[slot];
+  if (!M.active || !M.due) return;
+  const int old_len = M.plan_len, new_len = M.len, m = old_len - new_len;
+  if (m <= 0 || m > kMaxEvery) return;
+  const int64_t region = M.base + static_cast<int64_t>(lg) * M.cap;
+  PagedRows prow{};
+  if (threadIdx.x == 0)
+    s_chunk = static_cast<int>(__hip_atomic_fetch_add(sync_words + head, 1u, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT) & 31u);
+  if constexpr (PAGED) {
+    const int32_t* table = pg.tables + static_cast<int64_t>(slot) * pg.pages_per_seq;
+    const int n_pages = (old_len + (1 << pg.page_shift) - 1) >> pg.page_shift;
+    for (int i = threadIdx.x; i < n_pages; i += NT) tbl[i] = table[i];
+    __syncthreads();
+    prow = PagedRows{tbl, pg.group_rows, static_cast<int64_t>(lg) << pg.page_shift,
+                     pg.page_shift};
+  }
+  for (int k = threadIdx.x; k < m; k += NT) {
+    if constexpr (PAGED) f[k] = pos[prow(new_len + k)] - k;
+    else f[k] = pos[region + new_len + k] - k;
+  }
+  __syncthreads();
+  const int chunk = __builtin_amdgcn_readfirstlane(s_chunk);
+  const int d0 = __builtin_amdgcn_readfirstlane(f[0]);
+  const int j0 = (d0 & ~7) + chunk * kChunk;
+  if (j0 < new_len) {
+    const ChunkLoaded loaded{sync_words + head, chunk};
+    const int first = max(d0, j0), end = min(new_len, j0 + kChunk);
+    if constexpr (PAGED)
+      compact_rows<NT, E, false, PagedRows, false>(f, m, src_of, first, end, old_len, prow, kpool,
+                                                   vpool, nullptr, loaded);
+    else
+      // (the region is a multiple of a value tile: the rows count from it)
+      compact_rows<NT, E, false, RegionRows, false>(
+          f, m, src_of, first, end, old_len, RegionRows{0}, kpool + region * kHeadDim,
+          vpool + region * kHeadDim, nullptr, loaded);
+  }
+  if (threadIdx.x == 0) {
+    uint32_t* word = sync_words + head;
+    const uint32_t before =
+        __hip_atomic_fetch_add(word, 32u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (((before >> 5) & 31u) == static_cast<uint32_t>(n_chunks - 1))
+      __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
 template <int NT, int KPT, bool POS_ONLY, int LAYOUT>
 hipError_t launch_layout(const Shape& sh, const SeqMeta* meta, void* kpool,
                          void* vpool, int32_t* pos, int slot_lo, int slot_hi,
-                         hipStream_t s, int32_t* drops_out, int drop_stride) {
-  const dim3 grid((slot_hi - slot_lo) * sh.L * sh.Hkv);
+                         hipStream_t s, int32_t* drops_out, int drop_stride,
+                         bool lists_in_pos) {
+  const DueList due = sh.due ? *sh.due : DueList{};
+  const dim3 grid((due.n ? due.n : slot_hi - slot_lo) * sh.L * sh.Hkv);
   if (sh.dtype == 1) {
     hipLaunchKernelGGL((evict_kernel<NT, KPT, uint16_t, POS_ONLY, LAYOUT>), grid,
                        dim3(NT), 0, s, meta, static_cast<uint16_t*>(kpool),
                        static_cast<uint16_t*>(vpool), pos, sh.L, sh.Hkv, sh.r,
-                       slot_lo, sh.policy, sh.block, sh.pg, drops_out, drop_stride);
+                       slot_lo, sh.policy, sh.block, sh.pg, drops_out, drop_stride, due, lists_in_pos);
   } else {
     hipLaunchKernelGGL((evict_kernel<NT, KPT, float, POS_ONLY, LAYOUT>), grid,
                        dim3(NT), 0, s, meta, static_cast<float*>(kpool),
                        static_cast<float*>(vpool), pos, sh.L, sh.Hkv, sh.r,
-                       slot_lo, sh.policy, sh.block, sh.pg, drops_out, drop_stride);
+                       slot_lo, sh.policy, sh.block, sh.pg, drops_out, drop_stride, due, lists_in_pos);
   }
   return hipGetLastError();
 }
@@ -554,42 +667,66 @@ hipError_t launch_layout(const Shape& sh, const SeqMeta* meta, void* kpool,
 template <int NT, int KPT, bool POS_ONLY>
 hipError_t launch_kpt(const Shape& sh, const SeqMeta* meta, void* kpool,
                       void* vpool, int32_t* pos, int slot_lo, int slot_hi,
-                      hipStream_t s, int32_t* drops_out, int drop_stride) {
+                      hipStream_t s, int32_t* drops_out, int drop_stride,
+                      bool lists_in_pos) {
   if (sh.layout == 1)
     return launch_layout<NT, KPT, POS_ONLY, 1>(sh, meta, kpool, vpool, pos, slot_lo,
-                                               slot_hi, s, drops_out, drop_stride);
+                                               slot_hi, s, drops_out, drop_stride, lists_in_pos);
   if (sh.layout == 2)
     return launch_layout<NT, KPT, POS_ONLY, 2>(sh, meta, kpool, vpool, pos, slot_lo,
-                                               slot_hi, s, drops_out, drop_stride);
+                                               slot_hi, s, drops_out, drop_stride, lists_in_pos);
   return launch_layout<NT, KPT, POS_ONLY, 0>(sh, meta, kpool, vpool, pos, slot_lo,
-                                             slot_hi, s, drops_out, drop_stride);
+                                             slot_hi, s, drops_out, drop_stride, lists_in_pos);
 }
 
 template <bool POS_ONLY>
 hipError_t launch_mode(const Shape& sh, const SeqMeta* meta, void* kpool,
                        void* vpool, int32_t* pos, int slot_lo, int slot_hi,
                        int max_candidates, hipStream_t s, int32_t* drops_out,
-                       int drop_stride) {
+                       int drop_stride, bool lists_in_pos = false) {
   // 1,024 threads, KPT scores each: the smallest KPT that holds the
   // candidates (C = K + 64 at the usual budgets: K = 1,024 -> 2, 2,048 -> 3,
   // 4,096 -> 5, 8,192 -> 9).  More than 16 scores per thread is kept for the
   // largest budgets only: 32 unrolled Philox evaluations exceed the
   // compiler's unroll budget and the score array then lives in scratch memory.
   if (max_candidates <= 1024 * 1)
-    return launch_kpt<1024, 1, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride);
+    return launch_kpt<1024, 1, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride, lists_in_pos);
   if (max_candidates <= 1024 * 2)
-    return launch_kpt<1024, 2, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride);
+    return launch_kpt<1024, 2, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride, lists_in_pos);
   if (max_candidates <= 1024 * 3)
-    return launch_kpt<1024, 3, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride);
+    return launch_kpt<1024, 3, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride, lists_in_pos);
   if (max_candidates <= 1024 * 5)
-    return launch_kpt<1024, 5, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride);
+    return launch_kpt<1024, 5, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride, lists_in_pos);
   if (max_candidates <= 1024 * 9)
-    return launch_kpt<1024, 9, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride);
+    return launch_kpt<1024, 9, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride, lists_in_pos);
   if (max_candidates <= 1024 * 16)
-    return launch_kpt<1024, 16, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride);
+    return launch_kpt<1024, 16, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride, lists_in_pos);
   if (max_candidates <= kMaxCandidates)
-    return launch_kpt<1024, 32, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride);
+    return launch_kpt<1024, 32, POS_ONLY>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi, s, drops_out, drop_stride, lists_in_pos);
   return hipErrorInvalidValue;
+}
+
+// Workgroups per head of a split move (0: one workgroup selects and moves a
+// head).  Split when the due heads leave half of the CUs idle: with more heads, the moves keep HBM busy anyway and the selections overlap them
+// (128 paged heads: 12 + 87 us split, 100 us in one launch; 64: 65 and 86).
+// A head's moved rows lie in [prompt, prompt + candidates + recent rows).
+int move_chunks(const Shape& sh, int max_candidates) {
+  if (!sh.move_sync || !sh.due || sh.due->n == 0 || sh.layout == 1) return 0;
+  const int64_t heads = static_cast<int64_t>(sh.due->n) * sh.L * sh.Hkv;
+  if (heads >= 128 || heads > sh.move_words) return 0;
+  const int chunk = sh.dtype == 1 ? chunk_rows<1024, uint16_t>() : chunk_rows<1024, float>();
+  if (sh.every + 8 > chunk) return 0;    // an event drops up to `every` rows
+  const int n = (max_candidates + sh.r + 7 + chunk - 1) / chunk;
+  return n >= 2 && n <= kMaxChunks ? n : 0;
+}
+
+template <typename E, bool PAGED>
+void launch_chunks(const Shape& sh, const SeqMeta* meta, void* kpool, void* vpool,
+                   const int32_t* pos, int n_chunks, hipStream_t s) {
+  const dim3 grid(sh.due->n * sh.L * sh.Hkv * n_chunks);
+  hipLaunchKernelGGL((move_chunks_kernel<1024, E, PAGED>), grid, dim3(1024), 0, s, meta,
+                     static_cast<E*>(kpool), static_cast<E*>(vpool), pos, sh.L, sh.Hkv, n_chunks,
+                     *sh.due, sh.pg, sh.move_sync);
 }
 
 }  // namespace
@@ -615,6 +752,21 @@ hipError_t launch_evict(const Shape& sh, const SeqMeta* meta, void* kpool,
                         int max_candidates, bool positions_only,
                         hipStream_t s, int32_t* drops_out, int drop_stride) {
   if (slot_hi <= slot_lo) return hipSuccess;
+  const int n_chunks = positions_only ? 0 : move_chunks(sh, max_candidates);
+  if (n_chunks > 0) {
+    const hipError_t e = launch_mode<true>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi,
+                                           max_candidates, s, nullptr, 0, true);
+    if (e != hipSuccess) return e;
+    const bool paged = sh.layout == 2;
+    if (sh.dtype == 1) {
+      if (paged) launch_chunks<uint16_t, true>(sh, meta, kpool, vpool, pos, n_chunks, s);
+      else launch_chunks<uint16_t, false>(sh, meta, kpool, vpool, pos, n_chunks, s);
+    } else {
+      if (paged) launch_chunks<float, true>(sh, meta, kpool, vpool, pos, n_chunks, s);
+      else launch_chunks<float, false>(sh, meta, kpool, vpool, pos, n_chunks, s);
+    }
+    return hipGetLastError();
+  }
   if (positions_only)
     return launch_mode<true>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi,
                              max_candidates, s, drops_out, drop_stride);

@@ -63,12 +63,25 @@ struct Paging {
   int64_t group_rows = 0;           // rows of one page group: L * Hkv * page_rows
 };
 
+// Slots that an event concerns, when they are few: the launch then has
+// workgroups for these only (n = 0: every slot of the launch's range).
+constexpr int kDueList = 32;
+struct DueList {
+  int n = 0;
+  int slot[kDueList] = {};
+};
+
 struct Shape {
   int L, Hq, Hkv, G, r, every, dtype;  // dtype: 0 f32, 1 bf16
   int layout;                          // 0 chronological, 1 hole-fill, 2 paged
   int policy;                          // ra_policy
   int block;                           // tokens per block (block policy)
   Paging pg;                           // the paged layout's tables
+  const DueList* due = nullptr;        // events: the slots due, if listed
+  // full events: `move_words` words, zero between launches, with which the
+  // workgroups that share a head's move order themselves (evict.hip)
+  uint32_t* move_sync = nullptr;
+  int64_t move_words = 0;
 };
 
 // Pool row of row j of one (sequence, layer, KV head) cache.
