@@ -5,16 +5,28 @@
 // position as the sum of the attention weights of the last w queries,
 // max-pooled over neighbouring positions; Eq. 1 keeps the top-scoring
 // candidates (cached rows outside the r most recent).  Per (sequence, layer,
-// KV head), one 512-thread workgroup:
-//   pass 1: for every window query (G heads x 64 steps) the log-sum-exp of
-//           q.k/sqrt(d) over the cached rows at or before its position;
-//   pass 2: the same logits again, weights 2^(s - lse) summed over queries
-//           into a per-row score held in LDS;
+// KV head), one 1,024-thread workgroup:
+//   pass 1: for every window query (G heads x 64 steps) the softmax reference
+//           and sum of q.k/sqrt(d) over the cached rows at or before its
+//           position;
+//   pass 2: the same logits again, the weights summed over queries into a
+//           per-row score held in LDS;
 //   then max-pool over 7 rows, and the m lowest candidates (the same m as
 //   Random Attention drops at this event) by the shared radix select.
-// Keys stream through LDS in 64-row blocks (prefetched into registers while
-// the previous block is used); both logit passes run on
-// v_mfma_f32_16x16x32_bf16 with 16 queries x 16 keys per tile.
+// Both passes run on v_mfma_f32_16x16x32_bf16 with 16 queries x 16 keys per
+// tile.
+//
+// Bound by the vector work per logit (a fused multiply-add, an exponential at
+// a quarter of the rate, an addition), which the matrix products of the other
+// wavefronts of a SIMD run beside: a head has one workgroup, so it fills all
+// four wavefronts of every SIMD (128 registers each: two query tiles; three
+// spill).  They divide the query tiles and, where these are few, the keys of a
+// block between them, so that a key tile read from LDS serves two query tiles
+// (one: the LDS reads take longer than the logits).
+// Pass 1 keeps its reference as long as no logit passes it by more than 2^8,
+// instead of raising it in every block.  240 heads of 9,376 rows,
+// G = 4: 607 -> 440 us (G = 1: 240 -> 148 at 192 heads of 4,900 rows, G = 8: 466 ->
+// 404, G = 16, whose operands spilled: 4.4 -> 0.67 ms).
 #include <type_traits>
 
 #include "ra_internal.h"
@@ -27,12 +39,18 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kNT = 512;
+constexpr int kNT = 1024;
+constexpr int kWaves = kNT / 64;
+constexpr int kBlk = 128;         // key rows per LDS block
 constexpr int kWin = 64;          // window queries per query head
-constexpr int kBlk = 64;          // key rows per LDS block
 constexpr int kRowStride = 136;   // bf16 elements per LDS row (256 B + 16 B pad)
+constexpr int kTilesPerWave = 2;  // query tiles a wavefront holds in registers
 constexpr int kPoolHalf = 3;      // max-pool over 7 rows
 constexpr float kNegInf = -__builtin_huge_valf();
+// Pass 1 raises a query's reference when a logit exceeds it by more than this
+// many powers of two: the sums keep their relative precision, far from overflow.
+constexpr float kSlack = 8.f;
+constexpr float kNoReference = 3e38f;   // minus the reference of a query without keys
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
   bf16x8 r;
@@ -40,9 +58,31 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
   return r;
 }
 
+// LDS of a workgroup besides the scores: 87 KB, beside which the scores of the
+// longest cache (16,384 rows) take 64 of the 160 KB.  The sums of a block are
+// read while the next block's are written.
+struct Lds {
+  union {
+    struct {
+      uint16_t k[2][kBlk * kRowStride];
+      int pos[2][kBlk];
+      union {
+        float sums[2][kWaves][kBlk];             // [.][query group][key]
+        struct {
+          float off[kWaves][16], sum[kWaves][16];   // one tile of every wavefront
+        } merge;
+      };
+    } stream;
+    struct {
+      SelectShared sel;
+      int f[kMaxEvery];
+    } pick;
+  };
+};
+
 struct KBlock {
-  u32x4 u[2];   // this thread's two 16-byte pieces of a 64-row block
-  int p;        // position of row t (threads < 64)
+  u32x4 u[kBlk * 16 / kNT];   // this thread's 16-byte pieces of a block
+  int p;               // position of row t (threads < kBlk)
 };
 
 __device__ __forceinline__ void fetch_block(KBlock& b, const uint16_t* Kr,
@@ -50,8 +90,8 @@ __device__ __forceinline__ void fetch_block(KBlock& b, const uint16_t* Kr,
   const int t = threadIdx.x;
   const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int piece = t + q * kNT;          // 1024 pieces of 16 bytes
+  for (int q = 0; q < kBlk * 16 / kNT; ++q) {
+    const int piece = t + q * kNT;          // 16 pieces of 16 bytes to a row
     const int row = piece >> 4, col = piece & 15;
     b.u[q] = (kb + row < len)
         ? *reinterpret_cast<const u32x4*>(Kr + static_cast<int64_t>(kb + row) * kHeadDim + col * 8)
@@ -63,7 +103,7 @@ __device__ __forceinline__ void fetch_block(KBlock& b, const uint16_t* Kr,
 __device__ __forceinline__ void store_block(const KBlock& b, uint16_t* lk, int* lpos) {
   const int t = threadIdx.x;
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < kBlk * 16 / kNT; ++q) {
     const int piece = t + q * kNT;
     const int row = piece >> 4, col = piece & 15;
     *reinterpret_cast<u32x4*>(lk + row * kRowStride + col * 8) = b.u[q];
@@ -71,29 +111,25 @@ __device__ __forceinline__ void store_block(const KBlock& b, uint16_t* lk, int* 
   if (t < kBlk) lpos[t] = b.p;
 }
 
-// Waves of the workgroup; query tile j of wave w is tile j * kWaves + w
-// (round robin, so the tiles of G heads spread evenly over the four SIMDs).
-constexpr int kWaves = kNT / 64;
-
-// Stream the head's cached rows through LDS in 64-row blocks (the next
-// block prefetched into registers while the current one is used) and call
-// body(b, keys, positions) once per block, with the whole workgroup.
+// Stream the head's cached rows through LDS (the next block prefetched into
+// registers while the current one is used) and call body(b, keys, positions)
+// once per block, with the whole workgroup.
 template <typename Body>
 __device__ __forceinline__ void stream_blocks(const uint16_t* Kr, const int32_t* P, int len,
-                                              uint16_t (&lk)[2][kBlk * kRowStride],
-                                              int (&lpos)[2][kBlk], Body body) {
+                                              Lds& lds, Body body) {
+  auto& st = lds.stream;
   const int nblk = (len + kBlk - 1) / kBlk;
   KBlock nb;
   fetch_block(nb, Kr, P, 0, len);
-  __syncthreads();                 // the previous user of lk is done with it
-  store_block(nb, lk[0], lpos[0]);
+  __syncthreads();                 // the previous user of the buffers is done with them
+  store_block(nb, st.k[0], st.pos[0]);
   __syncthreads();
   for (int b = 0; b < nblk; ++b) {
     const int cur = b & 1;
     if (b + 1 < nblk) fetch_block(nb, Kr, P, (b + 1) * kBlk, len);
-    body(b, lk[cur], lpos[cur]);
+    body(b, st.k[cur], st.pos[cur]);
     // the other buffer was last read before the previous barrier
-    if (b + 1 < nblk) store_block(nb, lk[cur ^ 1], lpos[cur ^ 1]);
+    if (b + 1 < nblk) store_block(nb, st.k[cur ^ 1], st.pos[cur ^ 1]);
     __syncthreads();
   }
 }
@@ -107,28 +143,39 @@ __device__ __forceinline__ void load_kop(bf16x8 (&kop)[4], const uint16_t* lkb, 
   for (int s = 0; s < 4; ++s) kop[s] = as_bf16x8(*reinterpret_cast<const u32x4*>(krow + 32 * s));
 }
 
-// S^T tile: 16 window queries (rows) x 16 keys (columns); the lane holds
-// rows 4*grp + i of column qi.
-__device__ __forceinline__ f32x4 score_tile(const bf16x8 (&qop)[4], const bf16x8 (&kop)[4]) {
-  f32x4 d = {0.f, 0.f, 0.f, 0.f};
+// S^T tiles of two 16-key tiles: 16 window queries (rows) x 16 keys (columns)
+// each; the lane holds rows 4*grp + i of column qi.  All chains of products
+// advance together.
+template <int N>
+__device__ __forceinline__ void score_tiles(f32x4 (&x)[2][N],
+                                            const bf16x8 (&qop)[kTilesPerWave][4],
+                                            const uint16_t* lkb, int kt, int qi, int grp) {
+  bf16x8 kop[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    load_kop(kop[h], lkb, kt + h, qi, grp);
+#pragma unroll
+    for (int j = 0; j < N; ++j) x[h][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 #pragma unroll
   for (int s = 0; s < 4; ++s)
-    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qop[s], kop[s], d, 0, 0, 0);
-  return d;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        x[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qop[j][s], kop[h][s], x[h][j], 0, 0, 0);
 }
 
-template <int KPT, int TPW, int MINW>
-__global__ __launch_bounds__(kNT, MINW) void window_score_kernel(
+template <int KPT>
+__global__ __launch_bounds__(kNT) void window_score_kernel(
     const SeqMeta* __restrict__ meta, const uint16_t* __restrict__ kpool,
     const int32_t* __restrict__ pos, const uint16_t* __restrict__ qwin,
     float* __restrict__ scores_out, int32_t* __restrict__ drops_out,
     int scores_stride, int L, int Hq, int Hkv, int G, int r, int every,
     int slot_lo, float scale_log2) {
-  extern __shared__ float smem[];                 // scores [cap]
-  __shared__ uint16_t lk[2][kBlk * kRowStride];
-  __shared__ int lpos[2][kBlk];
-  __shared__ SelectShared sel_sh;
-  __shared__ int f[kMaxEvery];
+  extern __shared__ __align__(16) char smem[];
+  Lds& lds = *reinterpret_cast<Lds*>(smem);
+  float* score = reinterpret_cast<float*>(smem + sizeof(Lds));   // [len]
 
   const int per_seq = L * Hkv;
   const int slot = slot_lo + static_cast<int>(blockIdx.x) / per_seq;
@@ -142,153 +189,198 @@ __global__ __launch_bounds__(kNT, MINW) void window_score_kernel(
   const int64_t region = M.base + static_cast<int64_t>(lg) * M.cap;
   const uint16_t* Kr = kpool + region * kHeadDim;
   const int32_t* P = pos + region;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int qi = lane & 15, grp = lane >> 4;
-  float* score = smem;
   for (int i = t; i < len; i += kNT) score[i] = 0.f;
 
-  // window queries: tile qt covers head qt / 4, window rows 16 * (qt % 4) ..
-  // + 15; this wave's tiles are qt = j * kWaves + wave for j < ntile
-  const int n_tiles = G * 4;
-  // (uniform across the wave: readfirstlane lets the tile loops branch on
-  // scalars instead of masking lanes)
-  const int ntile = __builtin_amdgcn_readfirstlane(
-      wave < n_tiles ? min(TPW, (n_tiles - wave + kWaves - 1) / kWaves) : 0);
-  bf16x8 qop[TPW][4];
   const int first_pos = lp + M.step - kWin;     // position of window row 0
+  const int n_tiles = G * 4;
+  // rounds of as many query tiles as the wavefronts hold (one, up to G = 8)
+  for (int tile0 = 0, round = 0; tile0 < n_tiles; tile0 += round) {
+    // wavefront = key group * query groups + query group; key group kg takes
+    // the 16-key tiles [kg * tiles, (kg + 1) * tiles) of every block.  As many
+    // key groups as the round's query tiles leave wavefronts for, but two key
+    // tiles at least: G = 1 and 2: 4, G = 3 and 4: 2, more: 1.
+    round = min(n_tiles - tile0, kWaves * kTilesPerWave);
+    int qgroups = 4;
+    while (qgroups * kTilesPerWave < round) qgroups *= 2;
+    const int qg = wave % qgroups;
+    const int tiles = kBlk / 16 * qgroups / kWaves, kt0 = wave / qgroups * tiles;
+    // this wavefront's query tiles: qt = tile0 + j * qgroups + qg for j < ntile
+    // (round robin, so that they spread evenly over the SIMDs; one or two, as
+    // a round has at least qgroups tiles); tile qt covers head qt / 4, window
+    // rows 16 * (qt % 4) .. + 15
+    const int ntile = (round - qg + qgroups - 1) / qgroups;
+    const auto by_tiles = [&](auto&& work) {
+      if (ntile == kTilesPerWave) work(std::integral_constant<int, kTilesPerWave>{});
+      else work(std::integral_constant<int, kTilesPerWave - 1>{});
+    };
+    bf16x8 qop[kTilesPerWave][4];
 #pragma unroll
-  for (int j = 0; j < TPW; ++j) {
-    const int qt = j * kWaves + wave;
-    const bool ok = j < ntile;
-    const int head = g * G + (ok ? qt / 4 : 0);
-    const int row = 16 * ((ok ? qt : 0) % 4) + qi;
-    const uint16_t* qrow = qwin + ((static_cast<int64_t>(slot) * L + layer) * Hq + head) *
-                           kWin * kHeadDim + static_cast<int64_t>(row) * kHeadDim + 8 * grp;
+    for (int j = 0; j < kTilesPerWave; ++j) {
+      const int qt = j < ntile ? tile0 + j * qgroups + qg : 0;
+      const uint16_t* qrow =
+          qwin + ((static_cast<int64_t>(slot) * L + layer) * Hq + g * G + qt / 4) * kWin * kHeadDim +
+          static_cast<int64_t>(16 * (qt % 4) + qi) * kHeadDim + 8 * grp;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const u32x4 z = {0u, 0u, 0u, 0u};
-      qop[j][s] = as_bf16x8(ok ? *reinterpret_cast<const u32x4*>(qrow + 32 * s) : z);
+      for (int s = 0; s < 4; ++s)
+        qop[j][s] = as_bf16x8(*reinterpret_cast<const u32x4*>(qrow + 32 * s));
     }
-  }
-  // position of the lane's D-row i of tile j (its window query)
-  auto qpos = [&](int j, int i) {
-    return first_pos + 16 * ((j * kWaves + wave) % 4) + 4 * grp + i;
-  };
+    // position of the lane's D-row i of tile j (its window query)
+    auto qpos = [&](int j, int i) {
+      return first_pos + 16 * ((tile0 + j * qgroups + qg) % 4) + 4 * grp + i;
+    };
 
-  // pass 1: per (tile, D-row) running max (raw dot units) and sum of
-  // 2^((x - max) * scale) over this lane's key columns; every window query
-  // sees every key of a block unless the block reaches past the first window
-  // position (rows beyond len carry an infinite position): only then is the
-  // causal mask applied
-  float lse2[TPW][4];
-  {
-    float mx[TPW][4], sm[TPW][4];
+    // pass 1: per (tile, D-row) minus the reference (in log2 units) and the sum
+    // of 2^(x * scale - reference) over this lane's key columns; every window
+    // query sees every key of a block unless the block reaches past the first
+    // window position (rows beyond len carry an infinite position): only then
+    // is the causal mask applied
+    float off[kTilesPerWave][4], sum[kTilesPerWave][4];
 #pragma unroll
-    for (int j = 0; j < TPW; ++j)
+    for (int j = 0; j < kTilesPerWave; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        mx[j][i] = kNegInf;
-        sm[j][i] = 0.f;
+        off[j][i] = kNoReference;
+        sum[j][i] = 0.f;
       }
-    stream_blocks(Kr, P, len, lk, lpos, [&](int b, const uint16_t* lkb, const int* lpb) {
+    auto pass1_block = [&](const uint16_t* lkb, const int* lpb, auto count) {
+      constexpr int kTiles = decltype(count)::value;
       const bool masked = lpb[kBlk - 1] > first_pos;
-      float x[TPW][4][4];                        // [tile][subtile][D-row]
-#pragma unroll
-      for (int kt = 0; kt < kBlk / 16; ++kt) {
-        bf16x8 kop[4];
-        load_kop(kop, lkb, kt, qi, grp);
-#pragma unroll
-        for (int j = 0; j < TPW; ++j) {
-          if (j >= ntile) break;
-          const f32x4 d = score_tile(qop[j], kop);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) x[j][kt][i] = d[i];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < TPW; ++j) {
-        if (j >= ntile) break;
+      for (int kt = kt0; kt < kt0 + tiles; kt += 2) {
+        f32x4 x[2][kTiles];
+        score_tiles(x, qop, lkb, kt, qi, grp);
         if (masked) {
 #pragma unroll
-          for (int kt = 0; kt < kBlk / 16; ++kt) {
-            const int kpos = lpb[kt * 16 + qi];
+          for (int h = 0; h < 2; ++h) {
+            const int kpos = lpb[(kt + h) * 16 + qi];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (kpos > qpos(j, i)) x[j][kt][i] = kNegInf;
+            for (int j = 0; j < kTiles; ++j)
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                if (kpos > qpos(j, i)) x[h][j][i] = kNegInf;
           }
         }
+        // the largest exponent as an integer, whose order is the order of the
+        // positive values
+        float y[2][kTiles][4];
+        int top = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float bm = fmaxf(fmaxf(x[j][0][i], x[j][1][i]), fmaxf(x[j][2][i], x[j][3][i]));
-          const float mn = fmaxf(mx[j][i], bm);
-          // nothing visible yet (mn = -inf): every term below is 2^-inf = 0
-          const float off = mn == kNegInf ? 0.f : -mn * scale_log2;
-          float acc = sm[j][i] * __builtin_amdgcn_exp2f(fmaf(mx[j][i], scale_log2, off));
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-          for (int kt = 0; kt < kBlk / 16; ++kt)
-            acc += __builtin_amdgcn_exp2f(fmaf(x[j][kt][i], scale_log2, off));
-          sm[j][i] = acc;
-          mx[j][i] = mn;
+          for (int j = 0; j < kTiles; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              y[h][j][i] = fmaf(x[h][j][i], scale_log2, off[j][i]);
+              top = max(top, __float_as_int(y[h][j][i]));
+            }
+        if (__ballot(top > __float_as_int(kSlack))) {
+#pragma unroll
+          for (int j = 0; j < kTiles; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float o = fminf(off[j][i], -fmaxf(x[0][j][i], x[1][j][i]) * scale_log2);
+              sum[j][i] *= __builtin_amdgcn_exp2f(o - off[j][i]);
+              off[j][i] = o;
+#pragma unroll
+              for (int h = 0; h < 2; ++h) y[h][j][i] = fmaf(x[h][j][i], scale_log2, o);
+            }
         }
-      }
-    });
-    // merge the 16 lanes holding the same queries, then the log2-sum-exp
 #pragma unroll
-    for (int j = 0; j < TPW; ++j)
+        for (int j = 0; j < kTiles; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            sum[j][i] += __builtin_amdgcn_exp2f(y[0][j][i]) + __builtin_amdgcn_exp2f(y[1][j][i]);
+      }
+    };
+    stream_blocks(Kr, P, len, lds, [&](int, const uint16_t* lkb, const int* lpb) {
+      by_tiles([&](auto count) { pass1_block(lkb, lpb, count); });
+    });
+    // merge the 16 lanes holding the same queries, then the key groups; sum
+    // becomes the weights' factor 1 / sum (the stream ended with a barrier)
+    auto& mg = lds.stream.merge;
+#pragma unroll
+    for (int j = 0; j < kTilesPerWave; ++j) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float a_m = mx[j][i], a_s = sm[j][i];
+        float o = off[j][i], s = sum[j][i];
 #pragma unroll
-        for (int o = 1; o < 16; o <<= 1) {
-          const float b_m = __shfl_xor(a_m, o, 64), b_s = __shfl_xor(a_s, o, 64);
-          const float mn = fmaxf(a_m, b_m);
-          if (mn != kNegInf) {
-            a_s = a_s * __builtin_amdgcn_exp2f((a_m - mn) * scale_log2) +
-                  b_s * __builtin_amdgcn_exp2f((b_m - mn) * scale_log2);
-            a_m = mn;
-          }
+        for (int w = 1; w < 16; w <<= 1) {
+          const float o2 = __shfl_xor(o, w, 64), s2 = __shfl_xor(s, w, 64);
+          const float on = fminf(o, o2);
+          s = s * __builtin_amdgcn_exp2f(on - o) + s2 * __builtin_amdgcn_exp2f(on - o2);
+          o = on;
         }
-        lse2[j][i] = a_m * scale_log2 + __builtin_amdgcn_logf(a_s);
-      }
-  }
-
-  // pass 2: the same logits again; the weights 2^(s - lse) of every window
-  // query summed per key, one 16-key subtile at a time
-  auto pass2_block = [&](int b, const uint16_t* lkb, const int* lpb, auto masked) {
-#pragma unroll
-    for (int kt = 0; kt < kBlk / 16; ++kt) {
-      const int kpos = lpb[kt * 16 + qi];
-      bf16x8 kop[4];
-      load_kop(kop, lkb, kt, qi, grp);
-      // every tile's MFMA chain first, so the exponentials of one tile
-      // overlap the products of the next
-      f32x4 d[TPW];
-#pragma unroll
-      for (int j = 0; j < TPW; ++j) {
-        if (j >= ntile) break;
-        d[j] = score_tile(qop[j], kop);
-      }
-      float colsum = 0.f;
-#pragma unroll
-      for (int j = 0; j < TPW; ++j) {
-        if (j >= ntile) break;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float w = __builtin_amdgcn_exp2f(fmaf(d[j][i], scale_log2, -lse2[j][i]));
-          if constexpr (decltype(masked)::value) colsum += kpos > qpos(j, i) ? 0.f : w;
-          else colsum += w;
+        if (qi == 0) {
+          mg.off[wave][4 * grp + i] = o;
+          mg.sum[wave][4 * grp + i] = s;
         }
       }
-      colsum += __shfl_xor(colsum, 16, 64);
-      colsum += __shfl_xor(colsum, 32, 64);
-      const int key = b * kBlk + kt * 16 + qi;
-      if (grp == 0 && key < len) atomicAdd(&score[key], colsum);
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float o = kNoReference, s = 0.f;
+        for (int w = qg; w < kWaves; w += qgroups) o = fminf(o, mg.off[w][4 * grp + i]);
+        for (int w = qg; w < kWaves; w += qgroups)
+          s += mg.sum[w][4 * grp + i] * __builtin_amdgcn_exp2f(o - mg.off[w][4 * grp + i]);
+        off[j][i] = o;
+        sum[j][i] = s == 0.f ? 0.f : 1.f / s;
+      }
+      __syncthreads();
     }
-  };
-  stream_blocks(Kr, P, len, lk, lpos, [&](int b, const uint16_t* lkb, const int* lpb) {
-    if (lpb[kBlk - 1] > first_pos) pass2_block(b, lkb, lpb, std::true_type{});
-    else pass2_block(b, lkb, lpb, std::false_type{});
-  });
+
+    // pass 2: the same logits again; the weights of the wavefront's window
+    // queries summed per key
+    auto pass2_tiles = [&](const uint16_t* lkb, const int* lpb, float* out, auto count,
+                           auto masked) {
+      constexpr int kTiles = decltype(count)::value;
+      for (int kt = kt0; kt < kt0 + tiles; kt += 2) {
+        f32x4 d[2][kTiles];
+        score_tiles(d, qop, lkb, kt, qi, grp);
+        float colsum[2] = {0.f, 0.f};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int kpos = lpb[(kt + h) * 16 + qi];
+#pragma unroll
+          for (int j = 0; j < kTiles; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float w = __builtin_amdgcn_exp2f(fmaf(d[h][j][i], scale_log2, off[j][i]));
+              if constexpr (decltype(masked)::value)
+                colsum[h] += kpos > qpos(j, i) ? 0.f : w * sum[j][i];
+              else
+                colsum[h] = fmaf(w, sum[j][i], colsum[h]);
+            }
+        }
+        // over the four lane groups: even groups collect the first tile, odd
+        // ones the second
+        const bool odd = grp & 1;
+        float c = (odd ? colsum[1] : colsum[0]) + __shfl_xor(odd ? colsum[0] : colsum[1], 16, 64);
+        c += __shfl_xor(c, 32, 64);
+        if (grp < 2) out[(kt + grp) * 16 + qi] = c;
+      }
+    };
+    // the sums of block b over the query groups, in their order
+    auto add_block = [&](int b) {
+      const int key = b * kBlk + t;
+      if (t < kBlk && key < len) {
+        float s = score[key];
+        for (int w = 0; w < qgroups; ++w) s += lds.stream.sums[b % 2][w][t];
+        score[key] = s;
+      }
+    };
+    stream_blocks(Kr, P, len, lds, [&](int b, const uint16_t* lkb, const int* lpb) {
+      if (b > 0) add_block(b - 1);
+      float* out = lds.stream.sums[b % 2][qg];
+      by_tiles([&](auto count) {
+        if (lpb[kBlk - 1] > first_pos) pass2_tiles(lkb, lpb, out, count, std::true_type{});
+        else pass2_tiles(lkb, lpb, out, count, std::false_type{});
+      });
+    });
+    add_block((len - 1) / kBlk);
+  }
+  __syncthreads();
 
   const int64_t head_out = static_cast<int64_t>(slot - slot_lo) * per_seq + lg;
   if (scores_out) {
@@ -312,31 +404,10 @@ __global__ __launch_bounds__(kNT, MINW) void window_score_kernel(
       valid |= 1u << i;
     }
   }
-  const uint32_t drop = select_smallest<kNT, KPT, 32>(key, tie, valid, m, sel_sh);
-  drop_list<kNT, KPT>(drop, 0, f, sel_sh);
+  const uint32_t drop = select_smallest<kNT, KPT, 32>(key, tie, valid, m, lds.pick.sel);
+  int* f = lds.pick.f;
+  drop_list<kNT, KPT>(drop, 0, f, lds.pick.sel);
   for (int k = t; k < m; k += kNT) drops_out[head_out * every + k] = f[k] + k;
-}
-
-template <int KPT>
-hipError_t launch_tpw(int tpw, dim3 grid, size_t shmem, hipStream_t s,
-                      const SeqMeta* meta, const uint16_t* kpool, const int32_t* pos,
-                      const uint16_t* qwin, float* scores_out, int32_t* drops_out,
-                      int scores_stride, int L, int Hq, int Hkv, int G, int r, int every,
-                      int slot_lo, float scale) {
-  // up to two tiles per wave the build fits four waves per SIMD (two
-  // workgroups per CU, whose barriers do not keep them in step); more tiles
-  // need the registers of two waves per SIMD
-#define RA_WS_LAUNCH(T, W)                                                                  \
-  hipLaunchKernelGGL((window_score_kernel<KPT, T, W>), grid, dim3(kNT), shmem, s, meta,     \
-                     kpool, pos, qwin, scores_out, drops_out, scores_stride, L, Hq, Hkv,    \
-                     G, r, every, slot_lo, scale)
-  if (tpw <= 1) RA_WS_LAUNCH(1, 4);
-  else if (tpw <= 2) RA_WS_LAUNCH(2, 4);
-  else if (tpw <= 3) RA_WS_LAUNCH(3, 2);
-  else if (tpw <= 4) RA_WS_LAUNCH(4, 2);
-  else RA_WS_LAUNCH(8, 1);
-#undef RA_WS_LAUNCH
-  return hipGetLastError();
 }
 
 }  // namespace
@@ -347,22 +418,21 @@ hipError_t launch_window_score(const Shape& sh, const SeqMeta* meta, const void*
                                int slot_hi, int max_len, hipStream_t s) {
   if (slot_hi <= slot_lo) return hipSuccess;
   const dim3 grid((slot_hi - slot_lo) * sh.L * sh.Hkv);
-  const size_t shmem = sizeof(float) * static_cast<size_t>(max_len);
   const float scale = 1.4426950408889634f / sqrtf(static_cast<float>(kHeadDim));
-  const int tpw = (sh.G * 4 + kWaves - 1) / kWaves;
   const uint16_t* k = static_cast<const uint16_t*>(kpool);
   const uint16_t* q = static_cast<const uint16_t*>(qwin);
   const int n_cand = max_len;   // upper bound of len - r
-  if (n_cand <= kNT * 8)
-    return launch_tpw<8>(tpw, grid, shmem, s, meta, k, pos, q, scores_out, drops_out,
-                         scores_stride, sh.L, sh.Hq, sh.Hkv, sh.G, sh.r, sh.every, slot_lo, scale);
-  if (n_cand <= kNT * 16)
-    return launch_tpw<16>(tpw, grid, shmem, s, meta, k, pos, q, scores_out, drops_out,
-                          scores_stride, sh.L, sh.Hq, sh.Hkv, sh.G, sh.r, sh.every, slot_lo, scale);
-  if (n_cand <= kNT * 32)
-    return launch_tpw<32>(tpw, grid, shmem, s, meta, k, pos, q, scores_out, drops_out,
-                          scores_stride, sh.L, sh.Hq, sh.Hkv, sh.G, sh.r, sh.every, slot_lo, scale);
-  return hipErrorInvalidValue;
+  const size_t shmem = sizeof(Lds) + sizeof(float) * static_cast<size_t>(max_len);
+#define RA_WS_LAUNCH(K)                                                                    \
+  hipLaunchKernelGGL((window_score_kernel<K>), grid, dim3(kNT), shmem, s, meta, k, pos, q, \
+                     scores_out, drops_out, scores_stride, sh.L, sh.Hq, sh.Hkv, sh.G,      \
+                     sh.r, sh.every, slot_lo, scale)
+  if (n_cand <= kNT * 4) RA_WS_LAUNCH(4);
+  else if (n_cand <= kNT * 8) RA_WS_LAUNCH(8);
+  else if (n_cand <= kNT * 16) RA_WS_LAUNCH(16);
+  else return hipErrorInvalidValue;
+#undef RA_WS_LAUNCH
+  return hipGetLastError();
 }
 
 }  // namespace ra
