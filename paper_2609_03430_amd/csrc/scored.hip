@@ -14,6 +14,8 @@
 // head); candidates live in registers, KPT consecutive rows per thread.
 #include <math.h>
 
+#include <type_traits>
+
 #include "philox.h"
 #include "ra_internal.h"
 #include "select.h"
@@ -201,131 +203,223 @@ __global__ __launch_bounds__(kNT) void vase_kernel(
 
 constexpr int kRowTiles = 4;                          // 16-row tiles per wavefront
 constexpr int kChunkRows = (kNT / 64) * kRowTiles * 16;   // rows per workgroup: 512
+constexpr int kColBlk = 128;      // columns (cached keys) per LDS block
+constexpr int kColTiles = kColBlk / 16;
+constexpr int kColStride = 136;   // bf16 elements per LDS row (256 B + 16 B pad)
+constexpr int kXcds = 8;          // workgroups go to the dies round robin
 
-// Sum of squares of this lane's 32 channels of an operand row (8 per k-step).
-__device__ __forceinline__ float sumsq(const bf16x8 (&v)[4]) {
+// Sum of squares of 8 bf16 elements.
+__device__ __forceinline__ float sumsq8(u32x4 u) {
+  const bf16x8 v = as_bf16x8(u);
   float s = 0.f;
 #pragma unroll
-  for (int k = 0; k < 4; ++k)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float x = static_cast<float>(v[k][e]);
-      s = fmaf(x, x, s);
-    }
+  for (int e = 0; e < 8; ++e) {
+    const float x = static_cast<float>(v[e]);
+    s = fmaf(x, x, s);
+  }
   return s;
 }
 
-__device__ __forceinline__ void load_operand(bf16x8 (&v)[4], const uint16_t* Kr, int row,
-                                             int grp) {
+__device__ __forceinline__ float inv_norm(float sumsq) {
+  return sumsq > 0.f ? 1.f / sqrtf(sumsq) : 0.f;
+}
+
+constexpr int kPieces = kColBlk * kHeadDim / 8 / kNT;   // 16-byte pieces per thread and block
+static_assert(kPieces == 4, "store_cols deals four keys' norms to the lanes of a row");
+
+// This thread's pieces of the column block that starts at key kb (the 16
+// threads of a lane row hold one key; zeros past the last key).
+__device__ __forceinline__ void fetch_cols(u32x4 (&u)[kPieces], const uint16_t* Kr, int kb,
+                                           int len) {
 #pragma unroll
-  for (int s = 0; s < 4; ++s)
-    v[s] = as_bf16x8(*reinterpret_cast<const u32x4*>(
-        Kr + static_cast<int64_t>(row) * kHeadDim + 32 * s + 8 * grp));
+  for (int q = 0; q < kPieces; ++q) {
+    const int piece = threadIdx.x + q * kNT, row = kb + (piece >> 4);
+    const u32x4 z = {0u, 0u, 0u, 0u};
+    u[q] = row < len ? *reinterpret_cast<const u32x4*>(
+                           Kr + static_cast<int64_t>(row) * kHeadDim + (piece & 15) * 8)
+                     : z;
+  }
+}
+
+// The sum over the 16 lanes of a row, in every lane of it.
+__device__ __forceinline__ float row_sum(float x) {
+  const auto ror = [](float v, auto n) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v),
+                                                      0x120 + decltype(n)::value, 0xf, 0xf, false));
+  };
+  x += ror(x, std::integral_constant<int, 8>{});
+  x += ror(x, std::integral_constant<int, 4>{});
+  x += ror(x, std::integral_constant<int, 2>{});
+  x += ror(x, std::integral_constant<int, 1>{});
+  return x;
+}
+
+// The block into LDS, with 1 / norm of every key: one lane of a row for each of
+// its four keys.
+__device__ __forceinline__ void store_cols(const u32x4 (&u)[kPieces], uint16_t* lk,
+                                           float* linv) {
+  float ss[kPieces];
+#pragma unroll
+  for (int q = 0; q < kPieces; ++q) {
+    const int piece = threadIdx.x + q * kNT, row = piece >> 4;
+    *reinterpret_cast<u32x4*>(lk + row * kColStride + (piece & 15) * 8) = u[q];
+    ss[q] = row_sum(sumsq8(u[q]));
+  }
+  const int q = threadIdx.x & 3;
+  const float mine = q & 2 ? (q & 1 ? ss[3] : ss[2]) : (q & 1 ? ss[1] : ss[0]);
+  if ((threadIdx.x & 15) < kPieces) linv[(threadIdx.x + q * kNT) >> 4] = inv_norm(mine);
 }
 
 // cbar of the candidate rows [chunk * 512, chunk * 512 + 512) of one head.
 // D = K_rows . K_cols^T on v_mfma_f32_16x16x32_bf16: lane l holds rows
-// 4*(l/16) + i of a row tile and column l % 16 of a column tile; the four
-// lane groups hold a row's (or column's) channels in four parts of 32, so a
-// norm is a lane sum plus two shuffles.  Column tiles are swept from the
-// most recent (highest slot = highest position in the chronological layout)
-// down, so the first `recent_dups` near-duplicates a row meets are the ones
-// not counted; a ballot gives each row its near-duplicate columns in a tile.
-__global__ __launch_bounds__(kNT) void rkv_cbar_kernel(
+// 4*(l/16) + i of a row tile and column l % 16 of a column tile.  Columns are
+// swept from the most recent (highest slot = highest position in the
+// chronological layout) down, so the first `recent_dups` near-duplicates a
+// row meets are the ones not counted; a ballot gives each row its
+// near-duplicate columns in a tile.
+//
+// Bound by the matrix cores and the vector work per similarity together.  The
+// workgroup streams 128 columns at a time through LDS (the next block in
+// registers meanwhile), so a key is loaded and its norm taken once per 512
+// rows instead of once per 64, and a similarity that is not near a duplicate
+// costs a multiply, a fused add and half a maximum.  A wavefront's four row
+// tiles are four independent chains of products, the next column tile's
+// operand on its way from LDS meanwhile.  The chunks of a head run
+// on one die, whose L2 then holds its keys.  256 heads of 4,524 rows
+// (1.37 TFLOP of products): 2.65 -> 1.27 ms (1.08 PFLOP/s).
+__global__ __launch_bounds__(kNT, 2) void rkv_cbar_kernel(
     const SeqMeta* __restrict__ meta, const uint16_t* __restrict__ kpool,
-    float* __restrict__ cbar_out, int stride, int n_chunks, int L, int Hkv, int r,
+    float* __restrict__ cbar_out, int stride, int n_heads, int n_chunks, int L, int Hkv, int r,
     int slot_lo, float threshold, int recent_dups) {
-  const int head_idx = static_cast<int>(blockIdx.x) / n_chunks;
-  const int chunk = static_cast<int>(blockIdx.x) % n_chunks;
+  __shared__ uint16_t lk[2][kColBlk * kColStride];
+  __shared__ float linv[2][kColBlk];
+  const int die = static_cast<int>(blockIdx.x) % kXcds, nth = static_cast<int>(blockIdx.x) / kXcds;
+  const int head_idx = nth / n_chunks * kXcds + die;
+  const int chunk = nth % n_chunks;
+  if (head_idx >= n_heads) return;
   const int per_seq = L * Hkv;
   const int slot = slot_lo + head_idx / per_seq;
   const int lg = head_idx % per_seq;
   const SeqMeta& M = meta[slot];
   const int len = M.len, n_cand = M.len - r;
   if (!M.active || n_cand - (M.prompt_len + M.k_keep) <= 0) return;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (chunk * kChunkRows >= n_cand) return;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int qi = lane & 15, grp = lane >> 4;
   const int rt0 = (chunk * kChunkRows) / 16 + wave * kRowTiles;
-  if (rt0 * 16 >= n_cand) return;
+  const bool busy = rt0 * 16 < n_cand;   // past the candidates: a wavefront only loads
   const uint16_t* Kr = kpool + (M.base + static_cast<int64_t>(lg) * M.cap) * kHeadDim;
 
   bf16x8 a[kRowTiles][4];
-  float sum[kRowTiles][4], dup[kRowTiles][4], invr[kRowTiles][4];
+  float sum[kRowTiles][4], invr[kRowTiles][4];
   int found[kRowTiles][4];
 #pragma unroll
   for (int q = 0; q < kRowTiles; ++q) {
-    load_operand(a[q], Kr, min((rt0 + q) * 16 + qi, len - 1), grp);
-    float ss = sumsq(a[q]);
+    const uint16_t* row = Kr + static_cast<int64_t>(min((rt0 + q) * 16 + qi, len - 1)) * kHeadDim;
+    float ss = 0.f;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const u32x4 u = *reinterpret_cast<const u32x4*>(row + 32 * s + 8 * grp);
+      a[q][s] = as_bf16x8(u);
+      ss += sumsq8(u);
+    }
     ss += __shfl_xor(ss, 16, 64);
     ss += __shfl_xor(ss, 32, 64);
-    const float inv = ss > 0.f ? 1.f / sqrtf(ss) : 0.f;      // row qi of the tile
+    const float inv = inv_norm(ss);                          // row qi of the tile
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       sum[q][i] = 0.f;
-      dup[q][i] = 0.f;
       found[q][i] = 0;
       invr[q][i] = __shfl(inv, 4 * grp + i, 64);             // D-row 4*grp + i
     }
   }
-  const int n_ct = (len + 15) / 16;
-  bf16x8 b[4], bn[4];
-  load_operand(b, Kr, min((n_ct - 1) * 16 + qi, len - 1), grp);
-  for (int ct = n_ct - 1; ct >= 0; --ct) {
-    if (ct > 0) load_operand(bn, Kr, (ct - 1) * 16 + qi, grp);   // next tile in flight
-    const int col = ct * 16 + qi;
-    float ss = sumsq(b);
-    ss += __shfl_xor(ss, 16, 64);
-    ss += __shfl_xor(ss, 32, 64);
-    const float invc = ss > 0.f ? 1.f / sqrtf(ss) : 0.f;
-    float c[kRowTiles][4];
-    bool near = false;
+  const int n_blk = (len + kColBlk - 1) / kColBlk;
+  u32x4 next[kPieces];
+  fetch_cols(next, Kr, (n_blk - 1) * kColBlk, len);
+  store_cols(next, lk[0], linv[0]);
+  __syncthreads();
+  for (int b = n_blk - 1, cur = 0; b >= 0; --b, cur ^= 1) {
+    if (b > 0) fetch_cols(next, Kr, (b - 1) * kColBlk, len);   // next block in flight
+    if (busy) {
+      const uint16_t* krow = lk[cur] + qi * kColStride + 8 * grp;
+      const auto load_cols = [&](bf16x8 (&bop)[4], float& invc, int kt) {
 #pragma unroll
-    for (int q = 0; q < kRowTiles; ++q) {
-      f32x4 d = {0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < 4; ++s)
+          bop[s] = as_bf16x8(
+              *reinterpret_cast<const u32x4*>(krow + kt * 16 * kColStride + 32 * s));
+        invc = linv[cur][kt * 16 + qi];
+      };
+      // the last block's tiles past the last key hold zeros
+      bf16x8 bop[2][4];
+      float invc[2];
+      load_cols(bop[(kColTiles - 1) & 1], invc[(kColTiles - 1) & 1], kColTiles - 1);
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q][s], b[s], d, 0, 0, 0);
+      for (int kt = kColTiles - 1; kt >= 0; --kt) {
+        const int ct = b * kColTiles + kt;
+        if (kt > 0) load_cols(bop[(kt - 1) & 1], invc[(kt - 1) & 1], kt - 1);
+        f32x4 d[kRowTiles];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        c[q][i] = d[i] * invr[q][i] * invc;
-        near |= c[q][i] > threshold;
+        for (int q = 0; q < kRowTiles; ++q) d[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int q = 0; q < kRowTiles; ++q)
+            d[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q][s], bop[kt & 1][s], d[q], 0, 0, 0);
+        // a row's own column counts as nothing
+        if (ct >= rt0 && ct < rt0 + kRowTiles) {
+#pragma unroll
+          for (int q = 0; q < kRowTiles; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (ct == rt0 + q && 4 * grp + i == qi) d[q][i] = 0.f;
+        }
+        // every similarity into the sums; the largest x of the lane as an
+        // integer, whose order is the order of the positive values (a NaN is
+        // the largest)
+        const float ic = invc[kt & 1];
+        int top = 0;
+#pragma unroll
+        for (int q = 0; q < kRowTiles; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float x = d[q][i] * invr[q][i];
+            sum[q][i] = fmaf(x, ic, sum[q][i]);
+            top = max(top, __float_as_int(x));
+          }
+        // the few tiles with a near-duplicate take the recent ones out again.
+        // The factor ic is not negative: the largest similarity is that of `top`.
+        if (threshold < 0.f || __ballot(!(__int_as_float(top) * ic <= threshold))) {
+          const int col = ct * 16 + qi;
+#pragma unroll
+          for (int q = 0; q < kRowTiles; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int row = (rt0 + q) * 16 + 4 * grp + i;
+              const bool ok = col < len && col != row;
+              const float c = d[q][i] * invr[q][i] * ic;
+              const uint64_t bal = __ballot(ok && c > threshold);
+              const uint32_t bits = static_cast<uint32_t>(bal >> (16 * grp)) & 0xFFFFu;
+              const int need = recent_dups - found[q][i];
+              // this column is one of the row's `need` most recent duplicates here
+              const bool skip = need > 0 && ((bits >> qi) & 1u) && __popc(bits >> (qi + 1)) < need;
+              if (skip) sum[q][i] -= c;
+              if (need > 0) found[q][i] += min(need, __popc(bits));
+            }
+        }
       }
     }
-    // the last (ragged) column tile, the tiles holding a row's own column,
-    // and tiles with a near-duplicate take the full bookkeeping; the rest
-    // (nearly all) only accumulate
-    const bool edge = ct == n_ct - 1 || (ct >= rt0 && ct < rt0 + kRowTiles);
-    if (!edge && !__ballot(near)) {
-#pragma unroll
-      for (int q = 0; q < kRowTiles; ++q)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sum[q][i] += c[q][i];
-    } else {
-#pragma unroll
-      for (int q = 0; q < kRowTiles; ++q)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = (rt0 + q) * 16 + 4 * grp + i;
-          const bool ok = col < len && col != row;
-          if (ok) sum[q][i] += c[q][i];
-          const uint64_t bal = __ballot(ok && c[q][i] > threshold);
-          const uint32_t bits = static_cast<uint32_t>(bal >> (16 * grp)) & 0xFFFFu;
-          const int need = recent_dups - found[q][i];
-          if (need > 0 && bits) {
-            if (((bits >> qi) & 1u) && __popc(bits >> (qi + 1)) < need) dup[q][i] += c[q][i];
-            found[q][i] += min(need, __popc(bits));
-          }
-        }
-    }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) b[s] = bn[s];
+    // the other buffer was last read before the previous barrier
+    if (b > 0) store_cols(next, lk[cur ^ 1], linv[cur ^ 1]);
+    __syncthreads();
   }
+  if (!busy) return;
   float* out = cbar_out + static_cast<int64_t>(head_idx) * stride;
 #pragma unroll
   for (int q = 0; q < kRowTiles; ++q)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float v = sum[q][i] - dup[q][i];
+      float v = sum[q][i];
 #pragma unroll
       for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 64);
       const int row = (rt0 + q) * 16 + 4 * grp + i;
@@ -431,9 +525,10 @@ hipError_t launch_scored_select(const Shape& sh, int scorer, const SeqMeta* meta
   const int n_cand = max_len;   // upper bound of len - r
   if (scorer == 1) {
     const int n_chunks = (n_cand + kChunkRows - 1) / kChunkRows;
-    hipLaunchKernelGGL(rkv_cbar_kernel, dim3(heads * n_chunks), dim3(kNT), 0, s, meta,
+    const int groups = (heads + kXcds - 1) / kXcds * kXcds * n_chunks;
+    hipLaunchKernelGGL(rkv_cbar_kernel, dim3(groups), dim3(kNT), 0, s, meta,
                        static_cast<const uint16_t*>(kpool), cbar_scratch, score_stride,
-                       n_chunks, sh.L, sh.Hkv, sh.r, slot_lo, threshold, recent_dups);
+                       heads, n_chunks, sh.L, sh.Hkv, sh.r, slot_lo, threshold, recent_dups);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
