@@ -289,6 +289,55 @@ __device__ __forceinline__ void compact_rows(const int* f, int m, int* src_of, i
   }
 }
 
+// The keys of a thread's slots at positions tie[] (a slot that is no candidate
+// keeps a zero key, which the selection ignores), three Philox blocks in
+// lockstep: their independent rounds interleave, where one conditional draw
+// per candidate runs each 10-round chain of dependent multiplies on its own.
+// The policy is the same for the whole workgroup.
+template <int KPT>
+__device__ __forceinline__ void draw_keys(uint64_t (&score)[KPT], const uint32_t (&tie)[KPT],
+                                          uint32_t valid, int policy, int block, int lp,
+                                          int event, int layer, int g, uint64_t seed,
+                                          uint64_t rid) {
+  if (policy == 3) {
+#pragma unroll
+    for (int i = 0; i < KPT; ++i)
+      score[i] = (valid >> i) & 1 ? policy_key(3, block, static_cast<int>(tie[i]), lp, event,
+                                               layer, g, seed, rid)
+                                  : 0;
+    return;
+  }
+  int q[KPT];
+#pragma unroll
+  for (int i = 0; i < KPT; ++i) q[i] = static_cast<int>(tie[i]);
+  if (policy == 2) {
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) q[i] = draw_position(2, block, q[i], lp);
+  }
+  const uint64_t dl = policy == 1 ? 0 : static_cast<uint64_t>(layer);
+  const uint64_t dg = policy == 1 ? 0 : static_cast<uint64_t>(g);
+  constexpr int kWays = 3;
+#pragma unroll
+  for (int i0 = 0; i0 < KPT; i0 += kWays) {
+    uint64_t b[kWays], w[kWays][4];
+#pragma unroll
+    for (int j = 0; j < kWays; ++j)
+      b[j] = i0 + j < KPT ? static_cast<uint64_t>(q[i0 + j] >> 2) : 0;
+    philox_blocks<kWays>(b, static_cast<uint64_t>(event), dl, dg, seed, rid, w);
+#pragma unroll
+    for (int j = 0; j < kWays; ++j) {
+      if (i0 + j < KPT) {
+        // word k of the block, by masks (a select chain becomes branches)
+        const int i = i0 + j, k = q[i] & 3;
+        uint64_t x = 0;
+#pragma unroll
+        for (int n = 0; n < 4; ++n) x |= w[j][n] & (0ull - static_cast<uint64_t>(k == n));
+        score[i] = x & (0ull - static_cast<uint64_t>((valid >> i) & 1));
+      }
+    }
+  }
+}
+
 // LAYOUT: 0 chronological, 1 hole-fill, 2 chronological in pages.
 template <int NT, int KPT, typename E, bool POS_ONLY, int LAYOUT>
 __global__ __launch_bounds__(NT) void evict_kernel(
@@ -358,49 +407,8 @@ __global__ __launch_bounds__(NT) void evict_kernel(
       }
     }
   }
-  if (KPT <= 9) {
-    // The keys of every slot (a slot that is no candidate keeps a zero key,
-    // which the selection ignores), three Philox blocks in lockstep: their
-    // independent rounds interleave, where one conditional draw per candidate
-    // runs each 10-round chain of dependent multiplies on its own.  The
-    // policy is the same for the whole workgroup.
-    if (policy == 3) {
-#pragma unroll
-      for (int i = 0; i < KPT; ++i)
-        score[i] = (valid >> i) & 1 ? policy_key(3, block, static_cast<int>(tie[i]), lp, event,
-                                                 layer, g, seed, rid)
-                                    : 0;
-    } else {
-      int q[KPT];
-#pragma unroll
-      for (int i = 0; i < KPT; ++i) q[i] = static_cast<int>(tie[i]);
-      if (policy == 2) {
-#pragma unroll
-        for (int i = 0; i < KPT; ++i) q[i] = draw_position(2, block, q[i], lp);
-      }
-      const uint64_t dl = policy == 1 ? 0 : static_cast<uint64_t>(layer);
-      const uint64_t dg = policy == 1 ? 0 : static_cast<uint64_t>(g);
-      constexpr int kWays = 3;
-#pragma unroll
-      for (int i0 = 0; i0 < KPT; i0 += kWays) {
-        uint64_t b[kWays], w[kWays][4];
-#pragma unroll
-        for (int j = 0; j < kWays; ++j)
-          b[j] = i0 + j < KPT ? static_cast<uint64_t>(q[i0 + j] >> 2) : 0;
-        philox_blocks<kWays>(b, static_cast<uint64_t>(event), dl, dg, seed, rid, w);
-#pragma unroll
-        for (int j = 0; j < kWays; ++j) {
-          if (i0 + j < KPT) {
-            // word k of the block, by masks (a select chain becomes branches)
-            const int i = i0 + j, k = q[i] & 3;
-            uint64_t x = 0;
-#pragma unroll
-            for (int n = 0; n < 4; ++n) x |= w[j][n] & (0ull - static_cast<uint64_t>(k == n));
-            score[i] = x & (0ull - static_cast<uint64_t>((valid >> i) & 1));
-          }
-        }
-      }
-    }
+  if constexpr (KPT <= 9) {
+    draw_keys<KPT>(score, tie, valid, policy, block, lp, event, layer, g, seed, rid);
   }
 
   // 2. radix select of the m smallest (score, position); 3. drop list
@@ -496,6 +504,75 @@ __global__ __launch_bounds__(NT) void evict_kernel(
   else
     compact_rows<NT, E, POS_ONLY>(f, m, src_of, d0, new_len, old_len, RegionRows{region},
                                   kpool, vpool, P);
+}
+
+// n_steps decode steps of every active slot, positions only, with every event
+// that falls in them (the chronological layouts): one workgroup per head keeps
+// the generated positions in LDS from the first step to the last.  The slot
+// records are read, not changed.
+//
+// Bound by the draws (the vector ALU).  Event by event, each took three
+// launches (new positions, slot records, selection) and a pass over the
+// positions in memory, and with more heads than CUs every selection waited for
+// the last head of the one before: 1,024-thread workgroups run one to a CU.
+// 512 threads with twice the keys each run two, up to 3,072 rows.  96 events of 288 heads,
+// 2,112 candidates: 2.18 -> 1.36 ms.
+template <int NT, int KPT, bool PAGED>
+__global__ __launch_bounds__(NT, 4) void fast_forward_kernel(
+    const SeqMeta* __restrict__ meta, int32_t* __restrict__ pos, int Hkv, int per_seq, int r,
+    int every, int slot_lo, int n_steps, int policy, int block, Paging pg) {
+  extern __shared__ int32_t kept[];        // positions of rows lp, lp + 1, ..
+  __shared__ SelectShared sel_sh;
+  const int slot = slot_lo + static_cast<int>(blockIdx.x) / per_seq;
+  const int lg = static_cast<int>(blockIdx.x) % per_seq;
+  const int layer = lg / Hkv, g = lg % Hkv;
+  const SeqMeta& M = meta[slot];
+  if (!M.active) return;
+  const int t = threadIdx.x, lp = M.prompt_len, k_keep = M.k_keep;
+  const uint64_t seed = M.seed, rid = M.rid;
+  const RowMap rm = row_map(M, slot, lg, pg);
+  int n = M.len - lp, step = M.step, event = M.event;
+  for (int i = t; i < n; i += NT) kept[i] = pos[pool_row<PAGED>(rm, lp + i)];
+  for (int left = n_steps; left > 0;) {
+    const int run = min(left, every - step % every);
+    for (int i = t; i < run; i += NT) kept[n + i] = lp + step + i;
+    n += run;
+    step += run;
+    left -= run;
+    __syncthreads();
+    const int m = n - r - k_keep;
+    if (step % every != 0 || m <= 0) continue;
+    const int thr = lp + step - r;
+    uint64_t score[KPT];
+    uint32_t tie[KPT];
+    uint32_t valid = 0;
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {
+      const int c = t * KPT + i;
+      tie[i] = c < n ? static_cast<uint32_t>(kept[c]) : 0u;
+      score[i] = 0;
+      if (c < n && static_cast<int>(tie[i]) < thr) valid |= 1u << i;
+    }
+    draw_keys<KPT>(score, tie, valid, policy, block, lp, event, layer, g, seed, rid);
+    const uint32_t drop = select_smallest<NT, KPT, 64>(score, tie, valid, m, sel_sh);
+    // every position was read before the selection's barriers: a survivor goes
+    // straight to its slot less the drops below it
+    const int mine = __popc(drop), incl = wave_inclusive_scan(mine);
+    if ((t & 63) == 63) sel_sh.wave_tot[t >> 6] = incl;
+    __syncthreads();
+    int k = incl - mine;
+    for (int w = 0; w < (t >> 6); ++w) k += sel_sh.wave_tot[w];
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {
+      const int c = t * KPT + i;
+      if ((drop >> i) & 1) ++k;
+      else if (c < n) kept[c - k] = static_cast<int32_t>(tie[i]);
+    }
+    n -= m;
+    ++event;
+  }
+  __syncthreads();
+  for (int i = t; i < n; i += NT) pos[pool_row<PAGED>(rm, lp + i)] = kept[i];
 }
 
 // Compaction of a score-based round: each due head's drop list comes from
@@ -729,7 +806,38 @@ void launch_chunks(const Shape& sh, const SeqMeta* meta, void* kpool, void* vpoo
                      *sh.due, sh.pg, sh.move_sync);
 }
 
+template <int NT, int KPT>
+void launch_ff(const Shape& sh, const SeqMeta* meta, int32_t* pos, int slot_lo, int slot_hi,
+               int n_steps, int rows, hipStream_t s) {
+  const int per_seq = sh.L * sh.Hkv;
+  const dim3 grid((slot_hi - slot_lo) * per_seq);
+  const size_t lds = sizeof(int32_t) * static_cast<size_t>(rows);
+  if (sh.layout == 2)
+    hipLaunchKernelGGL((fast_forward_kernel<NT, KPT, true>), grid, dim3(NT), lds, s, meta,
+                       pos, sh.Hkv, per_seq, sh.r, sh.every, slot_lo, n_steps, sh.policy,
+                       sh.block, sh.pg);
+  else
+    hipLaunchKernelGGL((fast_forward_kernel<NT, KPT, false>), grid, dim3(NT), lds, s, meta,
+                       pos, sh.Hkv, per_seq, sh.r, sh.every, slot_lo, n_steps, sh.policy,
+                       sh.block, sh.pg);
+}
+
 }  // namespace
+
+hipError_t launch_fast_forward(const Shape& sh, const SeqMeta* meta, int32_t* pos, int slot_lo,
+                               int slot_hi, int n_steps, int rows, hipStream_t s) {
+  if (slot_hi <= slot_lo) return hipSuccess;
+  if (rows <= 512 * 2)
+    launch_ff<512, 2>(sh, meta, pos, slot_lo, slot_hi, n_steps, rows, s);
+  else if (rows <= 512 * 6)
+    launch_ff<512, 6>(sh, meta, pos, slot_lo, slot_hi, n_steps, rows, s);
+  else if (rows <= kMaxFastForwardRows)
+    launch_ff<1024, kMaxFastForwardRows / 1024>(sh, meta, pos, slot_lo, slot_hi, n_steps, rows,
+                                                s);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
 
 hipError_t launch_compact_drops(const Shape& sh, const SeqMeta* meta, void* kpool,
                                 void* vpool, int32_t* pos, const int32_t* drops,

@@ -126,6 +126,15 @@ hipError_t launch_evict(const Shape& sh, const SeqMeta* meta, void* kpool,
                         void* vpool, int32_t* pos, int slot_lo, int slot_hi,
                         int max_candidates, bool positions_only, hipStream_t s,
                         int32_t* drops_out = nullptr, int drop_stride = 0);
+// n_steps steps of the active slots of [lo, hi), positions only, events
+// included (the chronological layouts, a trigger period, and at most `rows`
+// <= kMaxFastForwardRows generated rows per head at any time); the slot
+// records follow with launch_replay_steps.
+constexpr int kMaxFastForwardRows = 1024 * 9;
+hipError_t launch_fast_forward(const Shape& sh, const SeqMeta* meta, int32_t* pos, int slot_lo,
+                               int slot_hi, int n_steps, int rows, hipStream_t s);
+hipError_t launch_replay_steps(SeqMeta* meta, int slot_lo, int slot_hi, int n_steps, int r,
+                               int every, hipStream_t s);
 // Deferred row moves: the drop lists of the last event, [max_seqs][L][Hkv]
 // [drop_stride] int32 (ascending slots), written by a positions-only event.
 // launch_mark_pending turns due == 1 into kDueMovePending for the active

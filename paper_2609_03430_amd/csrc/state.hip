@@ -48,6 +48,23 @@ __global__ void advance_kernel(SeqMeta* meta, int lo, int hi, int n_steps,
   meta[s] = M;
 }
 
+// advance_kernel over the runs between triggers that n_steps steps hold.
+__global__ void replay_steps_kernel(SeqMeta* meta, int lo, int hi, int n_steps, int r,
+                                    int every) {
+  const int s = lo + blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= hi) return;
+  SeqMeta M = meta[s];
+  if (!M.active) return;
+  for (int left = n_steps; left > 0;) {
+    const int run = min(left, every - M.step % every);
+    M.step += run;
+    M.len += run;
+    plan(M, r, M.step % every == 0);
+    left -= run;
+  }
+  meta[s] = M;
+}
+
 // The plan rule applied now to every active slot of [lo, hi).
 __global__ void plan_range_kernel(SeqMeta* meta, int lo, int hi, int r) {
   const int s = lo + blockIdx.x * blockDim.x + threadIdx.x;
@@ -246,6 +263,15 @@ hipError_t launch_advance(SeqMeta* meta, int slot_lo, int slot_hi, int n_steps,
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(advance_kernel, dim3((n + 255) / 256), dim3(256), 0, s,
                      meta, slot_lo, slot_hi, n_steps, r, every);
+  return hipGetLastError();
+}
+
+hipError_t launch_replay_steps(SeqMeta* meta, int slot_lo, int slot_hi, int n_steps, int r,
+                               int every, hipStream_t s) {
+  const int n = slot_hi - slot_lo;
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(replay_steps_kernel, dim3((n + 255) / 256), dim3(256), 0, s, meta, slot_lo,
+                     slot_hi, n_steps, r, every);
   return hipGetLastError();
 }
 

@@ -191,6 +191,41 @@ hipError_t launch_evict(const Shape& sh, const SeqMeta* meta, void*, void*, int3
   return hipSuccess;
 }
 
+hipError_t launch_fast_forward(const Shape& sh, const SeqMeta* meta, int32_t*, int slot_lo,
+                               int slot_hi, int n_steps, int rows, hipStream_t) {
+  if (slot_lo < 0 || slot_hi > g_max_seqs || slot_lo >= slot_hi || n_steps < 0)
+    fail("fast forward range", slot_lo, slot_hi);
+  check_chunk(sh, slot_lo, slot_hi, "fast forward launch over the per-launch bound");
+  if (rows < 0 || rows > kMaxFastForwardRows || sh.layout == 1 || sh.policy == 4)
+    fail("fast forward rows", rows, sh.layout);
+  for (int s = slot_lo; s < slot_hi; ++s) {
+    SeqMeta M = meta[s];          // every row it keeps on the way fits
+    if (!M.active) continue;
+    for (int i = 0; i < n_steps; ++i) {
+      ++M.step;
+      ++M.len;
+      if (M.len - M.prompt_len > rows) fail("fast forward keeps", M.len - M.prompt_len, rows);
+      plan(M, sh.r, M.step % sh.every == 0);
+    }
+    if (sh.layout == 2) M.cap = M.len;   // the device's record keeps the capacity of the start
+    check_rows(sh, M, s, M.len);  // and the rows it ends with have pages
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_replay_steps(SeqMeta* meta, int slot_lo, int slot_hi, int n_steps, int r,
+                               int every, hipStream_t) {
+  if (slot_lo < 0 || slot_hi > g_max_seqs || slot_lo > slot_hi || every < 1)
+    fail("replay range", slot_lo, slot_hi);
+  for (int s = slot_lo; s < slot_hi; ++s)
+    for (int i = 0; meta[s].active && i < n_steps; ++i) {
+      ++meta[s].step;
+      ++meta[s].len;
+      plan(meta[s], r, meta[s].step % every == 0);
+    }
+  return hipSuccess;
+}
+
 hipError_t launch_mark_pending(SeqMeta* meta, int slot_lo, int slot_hi, hipStream_t) {
   if (slot_lo < 0 || slot_hi > g_max_seqs) fail("mark range", slot_lo, slot_hi);
   for (int s = slot_lo; s < slot_hi; ++s)
