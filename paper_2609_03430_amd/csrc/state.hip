@@ -161,13 +161,14 @@ __global__ void write_rows_kernel(SeqMeta M, int slot, int len, Paging pg,
   }
 }
 
-// Rows [0, len) of one head to row-major outputs.  Grid: ceil(len/32), 128
-// threads.  One head is a short copy (1.6 MB at 3,136 bf16 rows), so its time
+// Rows [0, len) of one head to row-major outputs.  Grid: (ceil(len/32), 2): keys,
+// values; 128 threads.  One head is a short copy (1.6 MB at 3,136 bf16 rows), so its time
 // is the latency of a load and a store: every thread issues all its loads
 // before its stores, in 16-byte units (outputs are 16-byte aligned, as all
 // device pointers of the interface).  A thread takes kEpu channels x kEpu rows
 // of a value tile and transposes them in registers.  Element by element it
-// took 23 us per 3,136-row head, in 16-byte units 5.
+// took 23 us per 3,136-row head, in 16-byte units 5.5, keys and values side by
+// side 4.5.
 constexpr int kReadRows = 32;
 template <typename E, bool PAGED>
 __global__ __launch_bounds__(128) void read_rows_kernel(SeqMeta M, int slot, int lg, int len,
@@ -181,7 +182,8 @@ __global__ __launch_bounds__(128) void read_rows_kernel(SeqMeta M, int slot, int
   const RowMap rm = row_map(M, slot, lg, pg);
   const int j0 = blockIdx.x * kReadRows;                  // 32 rows lie in one page
   const int64_t row0 = pool_row<PAGED>(rm, j0);
-  if (k_out) {
+  if (blockIdx.y == 0) {
+    if (!k_out) return;
     u32x4 k[kPer];
     const u32x4* src = reinterpret_cast<const u32x4*>(kpool + row0 * kHeadDim);
     u32x4* dst = reinterpret_cast<u32x4*>(k_out + static_cast<int64_t>(j0) * kHeadDim);
@@ -196,6 +198,7 @@ __global__ __launch_bounds__(128) void read_rows_kernel(SeqMeta M, int slot, int
       const int u = threadIdx.x + i * 128;
       if (u < n) dst[u] = k[i];
     }
+    return;
   }
   if (!v_out) return;
   for (int u = threadIdx.x; u < kReadRows / kEpu * kUnitsRow; u += 128) {
@@ -334,7 +337,7 @@ template <typename E>
 void read_rows_t(const Shape& sh, const SeqMeta& M, int slot, int lg, int len,
                  const void* kpool, const void* vpool, void* k_out, void* v_out,
                  hipStream_t s) {
-  const dim3 grid((len + kReadRows - 1) / kReadRows);
+  const dim3 grid((len + kReadRows - 1) / kReadRows, 2);
   const E* k = static_cast<const E*>(kpool);
   const E* v = static_cast<const E*>(vpool);
   if (sh.pg.tables)
