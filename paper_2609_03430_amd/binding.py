@@ -157,9 +157,8 @@ def _check(status, where):
 
 
 def _ptr(t):
-    if t is None:
-        return None
-    return ctypes.c_void_p(t.data_ptr())
+    """A tensor's address; the entry points' argtypes turn it into a pointer."""
+    return None if t is None else t.data_ptr()
 
 
 # Config of every live handle, for the tensor checks below (the C ABI takes
@@ -198,10 +197,13 @@ def _arg(t, where, name, dtype=None, numel=0):
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the handle itself: building a Stream object takes longer than the rest of
+        # a call's host work (a one-layer step, a decode call and the end of the
+        # step: 15.8 us with it, 11.5 without)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
-        return ctypes.c_void_p(stream.cuda_stream)
-    return ctypes.c_void_p(int(stream))
+        return stream.cuda_stream
+    return int(stream)
 
 
 def make_config(num_layers, num_q_heads, num_kv_heads, budget_k, recent_r=64,
