@@ -1002,8 +1002,9 @@ ra_status ra_evict_now(ra_cache* c, int32_t seq, void* stream) {
 namespace {
 
 // Whether a fast forward runs as one launch (evict.hip): where it holds an
-// event (two events of 8 heads, 256 candidates: 13.0 us in one launch, 31.6 event
-// by event; of 288 heads, 8,256 candidates: 88 and 110; steps without one only
+// event (one event of 8 heads, 256 candidates: 9.8 us in one launch, 20 in three;
+// of 288 heads, 8,256 candidates: 50 and 57; eight events: 36 and 97, 316 and 420;
+// steps without one only
 // append), and not for hole-fill, whose positions are in no order, or caches over
 // the rows that the kernel keeps.  Paged: one sequence, whose page groups a shrink
 // returns and a growth takes again in the same order, so that its table holds
