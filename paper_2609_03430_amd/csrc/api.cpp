@@ -273,7 +273,7 @@ void mirror_plan(SeqMeta& M, int r, bool at_trigger) {
 // wavefronts built for one wavefront per SIMD (accumulators in the
 // accumulation registers) stream best; between 256 and 768 heads the 4-
 // wavefront build that fits three workgroups per CU keeps every head
-// resident at once.  fp32: see plan_f32.
+// resident at once, but see mid_plan.  fp32: see plan_f32.
 
 // A launch too small for 512 keys per CU (bf16): its time is the latency of
 // one round of loads and, for heads on several workgroups, of the merge, so
@@ -332,9 +332,35 @@ void plan_f32(Plan& p, int keys_max, int heads) {
   p.max_splits = (keys_max + p.split_keys - 1) / p.split_keys;
 }
 
+// Between 256 and 768 heads (bf16), long caches.  Microseconds per step:
+//   heads of about equal length take as long as the CUs with the most of them:
+//   two items per head even that out while there are few more heads than CUs
+//   (264 heads of 3,200 keys: 107 to 112 whole, 92 halved; 320: 115, 99; 384: 117 to
+//   120, 112; 440: 123, 131; 512: 137, 142; of 9,300 keys, 264: 305, 247; 384: 325,
+//   289; 512: 375, 379) and the halves are long (2,200 keys, 264: 68, 68; 384: 81, 93;
+//   1,600 keys, 264: 52, 57; 384: 63, 66);
+//   ragged heads of a contiguous layout stream better in the build for one
+//   wavefront per SIMD, as the many-headed launches do (2,200 to 4,200 keys, 264
+//   heads: 92.5, 90.6; 320: 125, 115; 384: 132, 127; 512: 148, 151; 640: 215,
+//   193; 760: 235, 218), paged ones do not (384: 133, 136), nor short ones (900
+//   keys, 320 heads: 40, 45).
+// The halves' partials must fit the no-alloc entry point's array, which whole
+// heads do not need.
+int mid_plan(const ra_cache* c, Plan& p, int heads, int keys_max, int64_t keys_mean) {
+  p.waves = 4;
+  if (keys_max < 3072) return 1;
+  if (8 * keys_mean < 7 * keys_max) {
+    p.wide_regs = !c->is_paged();
+    return 1;
+  }
+  const size_t halves = static_cast<size_t>(c->slot_hi) * c->cfg.num_kv_heads * 2 * c->G;
+  return heads < 400 && halves * (ra::kHeadDim + 2) * sizeof(float) <= ra::kNoAllocScratchBytes
+             ? 2 : 1;
+}
+
 // The plan for `n_active` sequences whose longest cache, the new row
-// included, has keys_max keys.
-Plan plan_for(const ra_cache* c, int keys_max, int n_active) {
+// included, has keys_max keys, and the mean one keys_mean.
+Plan plan_for(const ra_cache* c, int keys_max, int64_t keys_mean, int n_active) {
   const int heads = std::max(1, n_active * c->cfg.num_kv_heads);
   const bool bf16 = c->cfg.dtype == RA_BF16;
   Plan p;
@@ -344,7 +370,7 @@ Plan plan_for(const ra_cache* c, int keys_max, int n_active) {
       p.waves = 4;
       p.wide_regs = 1;
     } else if (heads > 256) {
-      p.waves = 4;
+      splits = mid_plan(c, p, heads, keys_max, keys_mean);
     } else {
       splits = std::max(1, (256 + heads / 2) / heads);
       const int keys = (keys_max + splits - 1) / splits;
@@ -381,12 +407,14 @@ Plan attention_plan(const ra_cache* c) {
   // that while sequences are younger than their budget no wavefront or split
   // is planned over rows that do not exist yet
   int keys_max = 32, n_active = 0;
+  int64_t keys = 0;
   for (int s = c->slot_lo; s < c->slot_hi; ++s) {
     if (!c->mirror[s].active) continue;
     keys_max = std::max(keys_max, c->mirror[s].len + 1);
+    keys += c->mirror[s].len + 1;
     ++n_active;
   }
-  return plan_for(c, keys_max, n_active);
+  return plan_for(c, keys_max, keys / std::max(1, n_active), n_active);
 }
 
 // Host checks shared by both attention entry points; nothing is launched.
@@ -939,17 +967,19 @@ ra_status ra_graph_mode(ra_cache* c, int32_t on, void* stream) {
     // up under the external policy need the host's capacity checks
     if (c->is_paged() || c->cfg.policy == RA_POLICY_EXTERNAL) return RA_ERR_UNSUPPORTED;
     int cap_max = 32, n_active = 0, candidates = 0;
+    int64_t caps = 0;
     for (int i = c->slot_lo; i < c->slot_hi; ++i) {
       const SeqMeta& M = c->mirror[i];
       if (!M.active) continue;
       cap_max = std::max(cap_max, M.cap);      // no cache outgrows its region
+      caps += M.cap;
       candidates = std::max(candidates, M.cap - M.prompt_len);
       ++n_active;
     }
     if (candidates > ra::kMaxCandidates) return RA_ERR_UNSUPPORTED;
     const ra_status fl = flush_pending(c, s);
     if (fl != RA_OK) return fl;
-    c->graph_plan = plan_for(c, cap_max, n_active);
+    c->graph_plan = plan_for(c, cap_max, caps / std::max(1, n_active), n_active);
     c->graph_candidates = candidates;
     c->graph = true;
     return RA_OK;
