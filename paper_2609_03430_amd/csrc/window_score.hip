@@ -25,7 +25,7 @@
 // (one: the LDS reads take longer than the logits).
 // Pass 1 keeps its reference as long as no logit passes it by more than 2^8,
 // instead of raising it in every block.  240 heads of 9,376 rows,
-// G = 4: 607 -> 440 us (G = 1: 240 -> 148 at 192 heads of 4,900 rows, G = 8: 466 ->
+// G = 4: 607 -> 440 to 457 us (G = 1: 240 -> 148 at 192 heads of 4,900 rows, G = 8: 466 ->
 // 404, G = 16, whose operands spilled: 4.4 -> 0.67 ms).
 #include <type_traits>
 
