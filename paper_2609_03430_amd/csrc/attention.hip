@@ -45,6 +45,12 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kNegInf = -__builtin_huge_valf();
 
+// The level that weights are taken against, for a state whose largest score is
+// m.  A state without a key of finite score (all masked, or all scores -inf)
+// takes 0 instead of -inf, which would make its weights and the rescale NaN;
+// they come out 0, and the state stays empty.
+__device__ __forceinline__ float reference(float m) { return m == kNegInf ? 0.f : m; }
+
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
   bf16x8 r;
   __builtin_memcpy(&r, &v, 16);
@@ -260,14 +266,14 @@ __device__ void merge_if_last(const AttnLaunch& a, int G, int Hq, int Hkv) {
       float mx = p.m;
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) mx = fmaxf(mx, m[j]);
-      const float keep = exp2f(p.m - mx);
+      const float ref = reference(mx), keep = exp2f(p.m - ref);
       p.m = mx;
       p.l *= keep;
       p.o0 *= keep;
       p.o1 *= keep;
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
-        const float w = s0 + j < hi ? exp2f(m[j] - mx) : 0.f;
+        const float w = s0 + j < hi ? exp2f(m[j] - ref) : 0.f;
         p.l += w * l[j];
         p.o0 += w * x[j];
         p.o1 += w * y[j];
@@ -300,7 +306,8 @@ __device__ void merge_if_last(const AttnLaunch& a, int G, int Hq, int Hkv) {
     Partial p = s_part[t];
     for (int k = 1; k < parts && k * per < nsplit; ++k) {
       const Partial r = s_part[k * pairs + t];
-      const float mx = fmaxf(p.m, r.m), wp = exp2f(p.m - mx), wr = exp2f(r.m - mx);
+      const float mx = fmaxf(p.m, r.m), ref = reference(mx);
+      const float wp = exp2f(p.m - ref), wr = exp2f(r.m - ref);
       p = Partial{mx, p.l * wp + r.l * wr, p.o0 * wp + r.o0 * wr, p.o1 * wp + r.o1 * wr};
     }
     put(t, p);
@@ -396,12 +403,7 @@ __device__ __forceinline__ void compute_block(Softmax& st, const BlockRegs& b,
   bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
   bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
   const float mn = fmaxf(st.m, bm);
-  // With MASKED, every key of a block can be masked while the state is still
-  // empty (a wavefront whose first rows were all dropped): the weights and
-  // the rescale are then taken against 0 instead of mn = -inf, which would
-  // make them NaN; they come out 0 and the state stays empty.  Unmasked
-  // blocks always hold a valid key.
-  const float mr = MASKED && mn == kNegInf ? 0.f : mn;
+  const float mr = reference(mn);
   const float alpha = exp2f(st.m - mr);
   // P = hi + lo, both bf16, so the weights keep ~16 significant bits through
   // the bf16 MFMA (the remainder of a bf16 rounding is exact in fp32)
@@ -1081,11 +1083,12 @@ __device__ __forceinline__ void compute_block(Softmax& st, const BlockF32& b,
   bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
   bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
   const float mn = fmaxf(st.m, bm);
-  const float alpha = exp2f(st.m - mn);
+  const float mr = reference(mn);
+  const float alpha = exp2f(st.m - mr);
   float p[4], psum = 0.f;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    p[i] = exp2f(x[i] - mn);
+    p[i] = exp2f(x[i] - mr);
     psum += p[i];
   }
   st.l = st.l * alpha + psum;
