@@ -45,11 +45,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kNegInf = -__builtin_huge_valf();
 
-// The level that weights are taken against, for a state whose largest score is
-// m.  A state without a key of finite score (all masked, or all scores -inf)
-// takes 0 instead of -inf, which would make its weights and the rescale NaN;
-// they come out 0, and the state stays empty.
-__device__ __forceinline__ float reference(float m) { return m == kNegInf ? 0.f : m; }
+// The largest score of a state that has seen none but -inf (masked keys, or rows
+// that score so): finite, so that the weights of such keys and the rescale come
+// out 0 and 1, where the difference of two infinities would make them NaN.
+constexpr float kNoScore = -3.4028234663852886e38f;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
   bf16x8 r;
@@ -254,7 +253,7 @@ __device__ void merge_if_last(const AttnLaunch& a, int G, int Hq, int Hkv) {
   const auto gather_by = [&](auto batch, int item, int lo, int hi) {
     constexpr int kBatch = decltype(batch)::value;
     const int q = item / (kHeadDim / 2), c = 2 * (item % (kHeadDim / 2));
-    Partial p{kNegInf, 0.f, 0.f, 0.f};
+    Partial p{kNoScore, 0.f, 0.f, 0.f};
     for (int s0 = lo; s0 < hi; s0 += kBatch) {
       float m[kBatch], l[kBatch], x[kBatch], y[kBatch];
 #pragma unroll
@@ -266,14 +265,14 @@ __device__ void merge_if_last(const AttnLaunch& a, int G, int Hq, int Hkv) {
       float mx = p.m;
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) mx = fmaxf(mx, m[j]);
-      const float ref = reference(mx), keep = exp2f(p.m - ref);
+      const float keep = exp2f(p.m - mx);
       p.m = mx;
       p.l *= keep;
       p.o0 *= keep;
       p.o1 *= keep;
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
-        const float w = s0 + j < hi ? exp2f(m[j] - ref) : 0.f;
+        const float w = s0 + j < hi ? exp2f(m[j] - mx) : 0.f;
         p.l += w * l[j];
         p.o0 += w * x[j];
         p.o1 += w * y[j];
@@ -306,8 +305,7 @@ __device__ void merge_if_last(const AttnLaunch& a, int G, int Hq, int Hkv) {
     Partial p = s_part[t];
     for (int k = 1; k < parts && k * per < nsplit; ++k) {
       const Partial r = s_part[k * pairs + t];
-      const float mx = fmaxf(p.m, r.m), ref = reference(mx);
-      const float wp = exp2f(p.m - ref), wr = exp2f(r.m - ref);
+      const float mx = fmaxf(p.m, r.m), wp = exp2f(p.m - mx), wr = exp2f(r.m - mx);
       p = Partial{mx, p.l * wp + r.l * wr, p.o0 * wp + r.o0 * wr, p.o1 * wp + r.o1 * wr};
     }
     put(t, p);
@@ -403,15 +401,14 @@ __device__ __forceinline__ void compute_block(Softmax& st, const BlockRegs& b,
   bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
   bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
   const float mn = fmaxf(st.m, bm);
-  const float mr = reference(mn);
-  const float alpha = exp2f(st.m - mr);
+  const float alpha = exp2f(st.m - mn);
   // P = hi + lo, both bf16, so the weights keep ~16 significant bits through
   // the bf16 MFMA (the remainder of a bf16 rounding is exact in fp32)
   bf16x8 p_hi, p_lo;
   float psum = 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const float pf = exp2f(x[e] - mr);
+    const float pf = exp2f(x[e] - mn);
     const __bf16 hi = static_cast<__bf16>(pf);
     p_hi[e] = hi;
     p_lo[e] = static_cast<__bf16>(pf - static_cast<float>(hi));
@@ -458,7 +455,7 @@ __device__ __forceinline__ void finish_item(const AttnLaunch& a, const Work& w, 
     float lsum = 0.f, o = 0.f;
 #pragma unroll
     for (int v = 0; v < W; ++v) {
-      const float sc = s_m[v][q] == kNegInf ? 0.f : exp2f(s_m[v][q] - mx);
+      const float sc = exp2f(s_m[v][q] - mx);
       lsum += s_l[v][q] * sc;
       o += s_o[v][q][c] * sc;
     }
@@ -542,7 +539,7 @@ __global__ __launch_bounds__(64 * W, MINW) void attn_bf16_kernel(
   }
 
   Softmax st;
-  st.m = kNegInf;
+  st.m = kNoScore;
   st.l = 0.f;
 #pragma unroll
   for (int u = 0; u < 8; ++u) st.acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -709,7 +706,7 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_short_kernel(
   };
 
   Softmax st;
-  st.m = kNegInf;
+  st.m = kNoScore;
   st.l = 0.f;
 #pragma unroll
   for (int u = 0; u < 8; ++u) st.acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -882,7 +879,7 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_move_kernel(
     }
   }
   Softmax st;
-  st.m = kNegInf;
+  st.m = kNoScore;
   st.l = 0.f;
 #pragma unroll
   for (int u = 0; u < 8; ++u) st.acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1021,7 +1018,7 @@ __global__ __launch_bounds__(64 * W, 1) void attn_bf16_move_kernel(
     float lsum = 0.f, o = 0.f;
 #pragma unroll
     for (int v = 0; v < W; ++v) {
-      const float sc = s_m[v][q] == kNegInf ? 0.f : exp2f(s_m[v][q] - mx);
+      const float sc = exp2f(s_m[v][q] - mx);
       lsum += s_l[v][q] * sc;
       o += s_o[v][q][c] * sc;
     }
@@ -1083,12 +1080,11 @@ __device__ __forceinline__ void compute_block(Softmax& st, const BlockF32& b,
   bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
   bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
   const float mn = fmaxf(st.m, bm);
-  const float mr = reference(mn);
-  const float alpha = exp2f(st.m - mr);
+  const float alpha = exp2f(st.m - mn);
   float p[4], psum = 0.f;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    p[i] = exp2f(x[i] - mr);
+    p[i] = exp2f(x[i] - mn);
     psum += p[i];
   }
   st.l = st.l * alpha + psum;
@@ -1147,7 +1143,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnLaunch a, Paging p
   };
 
   Softmax st;
-  st.m = kNegInf;
+  st.m = kNoScore;
   st.l = 0.f;
 #pragma unroll
   for (int u = 0; u < 8; ++u) st.acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
