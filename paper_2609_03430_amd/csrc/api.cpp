@@ -340,17 +340,24 @@ void plan_f32(Plan& p, int keys_max, int heads) {
 //   289; 512: 375, 379) and the halves are long (2,200 keys, 264: 68, 68; 384: 81, 93;
 //   1,600 keys, 264: 52, 57; 384: 63, 66);
 //   ragged heads of a contiguous layout stream better in the build for one
-//   wavefront per SIMD, as the many-headed launches do (2,200 to 4,200 keys, 264
-//   heads: 92.5, 90.6; 320: 125, 115; 384: 132, 127; 512: 148, 151; 640: 215,
-//   193; 760: 235, 218), paged ones do not (384: 133, 136), nor short ones (900
-//   keys, 320 heads: 40, 45).
+//   wavefront per SIMD, as the many-headed launches do, where they are long and
+//   the longest, which ends the launch and is read more slowly by that build, is
+//   not far above the mean (mean and longest cache, both builds: 264 heads of 2,570
+//   and 4,000 rows: 101, 98; 384 of 3,020 and 4,200: 129, 122; but 264 of 2,080 and
+//   4,000: 90, 93; of 3,210 and 9,000: 151, 165; of 1,000 and 4,000: 69, 78; 512 of
+//   3,010 and 4,200: 146, 149).  Past two heads per CU the launch outlasts its
+//   longest head by more (640 heads of 1,530 and 4,000: 138, 127; of 3,070 and
+//   9,000: 272, 238; but of 940 and 4,000: 108, 112; of 1,590 and 9,000: 188, 200).
+//   Paged heads do not gain (384: 133, 136).
 // The halves' partials must fit the no-alloc entry point's array, which whole
 // heads do not need.
 int mid_plan(const ra_cache* c, Plan& p, int heads, int keys_max, int64_t keys_mean) {
   p.waves = 4;
   if (keys_max < 3072) return 1;
   if (8 * keys_mean < 7 * keys_max) {
-    p.wide_regs = !c->is_paged();
+    const bool even = heads < 512 && keys_mean >= 2048 && 4 * int64_t(keys_max) <= 7 * keys_mean;
+    const bool many = heads >= 576 && keys_mean >= 1400 && keys_max <= 3 * keys_mean;
+    p.wide_regs = !c->is_paged() && (even || many);
     return 1;
   }
   const size_t halves = static_cast<size_t>(c->slot_hi) * c->cfg.num_kv_heads * 2 * c->G;

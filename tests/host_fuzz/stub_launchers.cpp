@@ -126,6 +126,9 @@ extern "C" int stub_check_tables(const int* active, const int* caps, int n) {
   return 0;
 }
 
+// The last attention launch of the process, for the tests of the launch plan.
+ra::AttnLaunch g_attention;
+
 extern "C" hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes,
                                      hipMemcpyKind, hipStream_t) {
   if (bytes) std::memcpy(dst, src, bytes);
@@ -291,6 +294,7 @@ hipError_t launch_table_set(const Shape& sh, const TableEntry* entries, int n, h
 }
 
 hipError_t launch_attention(const Shape& sh, const AttnLaunch& a, hipStream_t) {
+  g_attention = a;
   if (a.layer < 0 || a.layer >= sh.L) fail("attention layer", a.layer, sh.L);
   // the launched slots: [0, slot_hi) of the active range
   if (a.max_seqs < 1 || a.max_seqs > g_max_seqs) fail("attention slots", a.max_seqs, g_max_seqs);

@@ -1,0 +1,62 @@
+"""The launch plan's rules, on both sides of each line (CPU only): api.cpp
+built for the host, with the stand-ins of tests/host_fuzz for the launches."""
+
+import json
+import os
+import subprocess
+
+import pytest
+
+from paper_2609_03430_amd import binding as B
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2609_03430_amd", "csrc")
+FUZZ = os.path.join(ROOT, "tests", "host_fuzz")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CHRON, PAGED = B.RA_LAYOUT_CHRONOLOGICAL, B.RA_LAYOUT_PAGED
+
+pytestmark = pytest.mark.skipif(
+    not (os.path.exists(HIPCC) and os.path.isdir(FUZZ)), reason="hipcc or the stand-ins missing")
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan_rules")
+    objs = []
+    for src in (os.path.join(CSRC, "api.cpp"), os.path.join(FUZZ, "stub_launchers.cpp"),
+                os.path.join(FUZZ, "plan_rules.cpp")):
+        objs.append(str(d / (os.path.basename(src) + ".o")))
+        subprocess.run([HIPCC, "-x", "hip", "--cuda-host-only", "-O1", "-std=c++17",
+                        "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-c", src, "-o",
+                        objs[-1]], check=True, capture_output=True)
+    exe = str(d / "plan_rules")
+    subprocess.run(["g++", "-no-pie"] + objs + ["-o", exe], check=True, capture_output=True)
+
+    def launches(lens, dtype=B.RA_BF16, layout=CHRON, q_heads=40, kv_heads=8, budget=64, recent=64,
+                 every=64, forward=0, steps=1):
+        args = [dtype, layout, q_heads, kv_heads, budget, recent, every, forward, steps] + lens
+        r = subprocess.run([exe] + [str(a) for a in args], capture_output=True, text=True,
+                           timeout=60)
+        assert r.returncode == 0, r.stderr
+        return [json.loads(line) for line in r.stdout.splitlines()]
+    return launches
+
+
+def _ragged(n, mean, longest):
+    """n caches of about the mean length, one of them the longest."""
+    short = (mean * n - longest) // (n - 1)
+    return [short] * (n - 1) + [longest]
+
+
+@pytest.mark.parametrize("n,mean,longest,layout,wide", [
+    (33, 1000, 4000, CHRON, 0), (33, 2080, 4000, CHRON, 0), (33, 3200, 9000, CHRON, 0),
+    (33, 2570, 4000, CHRON, 1), (33, 5200, 9000, CHRON, 1), (33, 2570, 4000, PAGED, 0),
+    (64, 1600, 9000, CHRON, 0), (64, 1530, 4000, CHRON, 0), (48, 3020, 4200, CHRON, 1), (64, 3010, 4200, CHRON, 0),
+    (80, 940, 4000, CHRON, 0), (80, 1530, 4000, CHRON, 1), (80, 3070, 9000, CHRON, 1),
+    (80, 1590, 9000, CHRON, 0), (95, 1530, 4000, PAGED, 0),
+])
+def test_wide_registers_by_mean_and_longest(plans, n, mean, longest, layout, wide):
+    """One long prompt among short caches does not take the build for one
+    wavefront per SIMD, which reads it more slowly."""
+    a = plans(_ragged(n, mean, longest), layout=layout)[0]
+    assert (a["waves"], a["splits"], a["wide"]) == (4, 1, wide)
