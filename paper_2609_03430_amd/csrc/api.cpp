@@ -334,11 +334,11 @@ void plan_f32(Plan& p, int keys_max, int heads) {
 
 // Between 256 and 768 heads (bf16), long caches.  Microseconds per step:
 //   heads of about equal length take as long as the CUs with the most of them:
-//   two items per head even that out while there are few more heads than CUs
-//   (264 heads of 3,200 keys: 107 to 112 whole, 92 halved; 320: 115, 99; 384: 117 to
-//   120, 112; 440: 123, 131; 512: 137, 142; of 9,300 keys, 264: 305, 247; 384: 325,
-//   289; 512: 375, 379) and the halves are long (2,200 keys, 264: 68, 68; 384: 81, 93;
-//   1,600 keys, 264: 52, 57; 384: 63, 66);
+//   two items per head even that out while all of them are resident at once, three
+//   to a CU, 384 heads (264 heads of 3,200 keys: 113 whole, 96 halved; 320: 116, 104;
+//   384: 127, 115 to 127; 392: 122, 128; 512: 137, 142; of 9,000 keys, 264: 293, 241;
+//   384: 324, 283; 392: 314, 334; 512: 375, 379) and the halves are long (2,200 keys,
+//   264: 68, 68; 384: 81, 93; 1,600 keys, 264: 52, 57; 384: 63, 66);
 //   ragged heads of a contiguous layout stream better in the build for one
 //   wavefront per SIMD, as the many-headed launches do, where they are long and
 //   the longest, which ends the launch and is read more slowly by that build, is
@@ -361,7 +361,7 @@ int mid_plan(const ra_cache* c, Plan& p, int heads, int keys_max, int64_t keys_m
     return 1;
   }
   const size_t halves = static_cast<size_t>(c->slot_hi) * c->cfg.num_kv_heads * 2 * c->G;
-  return heads < 400 && halves * (ra::kHeadDim + 2) * sizeof(float) <= ra::kNoAllocScratchBytes
+  return heads <= 384 && halves * (ra::kHeadDim + 2) * sizeof(float) <= ra::kNoAllocScratchBytes
              ? 2 : 1;
 }
 

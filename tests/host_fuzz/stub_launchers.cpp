@@ -176,10 +176,13 @@ hipError_t launch_append_positions(const Shape&, const SeqMeta* meta, int32_t*, 
   return hipSuccess;
 }
 
-// The test build cuts per-head launches into chunks of at most 3 heads, or
+// The fuzzer's build cuts per-head launches into chunks of at most 3 heads, or
 // one slot where a slot has more (RA_MAX_HEADS_PER_LAUNCH=3).
+#ifndef RA_MAX_HEADS_PER_LAUNCH
+#define RA_MAX_HEADS_PER_LAUNCH (1 << 20)
+#endif
 void check_chunk(const Shape& sh, int slot_lo, int slot_hi, const char* what) {
-  if (slot_hi - slot_lo > 1 && (slot_hi - slot_lo) * sh.L * sh.Hkv > 3)
+  if (slot_hi - slot_lo > 1 && (slot_hi - slot_lo) * sh.L * sh.Hkv > RA_MAX_HEADS_PER_LAUNCH)
     fail(what, slot_lo, slot_hi);
 }
 

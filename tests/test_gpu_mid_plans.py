@@ -1,7 +1,7 @@
 """Attention plans of 257 to 767 heads: long heads of about equal length are
-halved while there are fewer than 400, ragged ones of a contiguous layout take
-the build for one wavefront per SIMD, the rest is whole.  Outputs, events and
-rows against the oracle for the cases on both sides of each line."""
+halved up to 384 of them, long ragged ones of a contiguous layout take the build
+for one wavefront per SIMD, the rest is whole.  Outputs, events and rows against
+the oracle for the cases on both sides of each line."""
 
 import numpy as np
 import pytest
@@ -19,8 +19,8 @@ CHRON, HOLE, PAGED = B.RA_LAYOUT_CHRONOLOGICAL, B.RA_LAYOUT_HOLE_FILL, B.RA_LAYO
     (33, 8, 20, 20, 3072, CHRON, 2),      # an event's moves cannot ride a halved head's step
     (33, 8, 20, 20, 3071, CHRON, 1),
     (65, 4, 0, 150, 3300, PAGED, 2),
-    (39, 10, 31, 31, 3100, HOLE, 2),      # 390 heads
-    (50, 8, 31, 31, 3100, CHRON, 1),      # 400
+    (48, 8, 31, 31, 3100, HOLE, 2),       # 384 heads
+    (39, 10, 31, 31, 3100, CHRON, 1),     # 390
     (33, 8, 0, 1900, 3200, CHRON, 1),     # ragged
     (33, 8, 0, 1900, 3200, PAGED, 1),
 ])

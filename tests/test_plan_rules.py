@@ -60,3 +60,13 @@ def test_wide_registers_by_mean_and_longest(plans, n, mean, longest, layout, wid
     wavefront per SIMD, which reads it more slowly."""
     a = plans(_ragged(n, mean, longest), layout=layout)[0]
     assert (a["waves"], a["splits"], a["wide"]) == (4, 1, wide)
+
+
+@pytest.mark.parametrize("n,kv_heads,layout,splits", [
+    (33, 8, CHRON, 2), (48, 8, CHRON, 2), (38, 10, PAGED, 2),
+    (39, 10, CHRON, 1), (49, 8, CHRON, 1), (49, 8, PAGED, 1), (64, 8, CHRON, 1),
+])
+def test_heads_halved_while_all_items_are_resident(plans, n, kv_heads, layout, splits):
+    """Two items per head up to 384 heads: three workgroups fit a CU."""
+    a = plans([3200] * n, layout=layout, kv_heads=kv_heads)[0]
+    assert (a["waves"], a["splits"], a["wide"]) == (4, splits, 0)
