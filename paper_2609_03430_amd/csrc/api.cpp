@@ -141,6 +141,9 @@ struct Plan {
   int split_keys = 0, max_splits = 0, waves = 1, wide_regs = 0;
   int group_waves = 0;
   int short_runs = 0;   // every item is at most 64 keys: the latency build
+  // an event of every sequence may leave its row moves to the next step's
+  // attention, one workgroup per head (attn_bf16_move_kernel)
+  bool whole = false;
   // partial slots per head that the no-alloc entry point's limit counts (at
   // least the workgroups of a head)
   int partials = 0;
@@ -372,12 +375,14 @@ Plan plan_for(const ra_cache* c, int keys_max, int64_t keys_mean, int n_active) 
   const bool bf16 = c->cfg.dtype == RA_BF16;
   Plan p;
   int splits = 1;
+  bool halved = false;
   if (bf16) {
     if (heads >= 768) {
       p.waves = 4;
       p.wide_regs = 1;
     } else if (heads > 256) {
       splits = mid_plan(c, p, heads, keys_max, keys_mean);
+      halved = splits == 2 && c->cfg.attn_split == 0;
     } else {
       splits = std::max(1, (256 + heads / 2) / heads);
       const int keys = (keys_max + splits - 1) / splits;
@@ -405,6 +410,11 @@ Plan plan_for(const ra_cache* c, int keys_max, int64_t keys_mean, int n_active) 
       p.max_splits = (keys_max + p.split_keys - 1) / p.split_keys;
     }
   }
+  // halved heads too: an event's own moves read and write every row again (384
+  // heads of 3,200 keys, an event every 16 steps: 137 us per step whole, 137 halved
+  // with the moves in the next step's attention, 140 with moves of its own; of
+  // 6,000 every 64: 218, 199, 204)
+  p.whole = halved || p.max_splits == 1;
   return p;
 }
 
@@ -499,11 +509,11 @@ ra_status launch_decode(ra_cache* c, int32_t layer, const void* q, const void* k
       if (e != hipSuccess) return hip_fail(e);
     }
   }
-  // rows of deferred events move in this step's attention when every head is
-  // one work item; otherwise they move first, on their own
+  // rows of deferred events move in this step's attention where the plan
+  // allows one workgroup per head; otherwise they move first, on their own
   bool move = false;
   if (c->any_pending()) {
-    if (plan.max_splits == 1) {
+    if (plan.whole) {
       move = true;
     } else {
       const ra_status st = flush_pending(c, stream);
@@ -536,6 +546,7 @@ ra_status launch_decode(ra_cache* c, int32_t layer, const void* q, const void* k
   if (move) {
     a.move = 1;
     a.waves = 8;
+    a.max_splits = 1;
     a.drops = c->drops;
     a.drop_stride = c->cfg.evict_every;
   }
@@ -938,7 +949,7 @@ ra_status ra_end_step(ra_cache* c, void* stream, int32_t* n_evicted) {
   }
   if (due) {
     // When every active sequence evicts at this step and the next step's
-    // attention gives every head one work item, the event only selects
+    // attention may give every head one workgroup, the event only selects
     // (positions compacted, each head's drop list kept) and that attention,
     // which reads every row anyway, moves the key/value rows
     // (attn_bf16_move_kernel): the rows are read once instead of twice.
@@ -946,7 +957,7 @@ ra_status ra_end_step(ra_cache* c, void* stream, int32_t* n_evicted) {
     // that steps of heads with nothing to move run the streaming kernel.
     int n_active = 0;
     for (int i = c->slot_lo; i < c->slot_hi; ++i) n_active += c->mirror[i].active;
-    const bool defer = c->drops && due == n_active && attention_plan(c).max_splits == 1;
+    const bool defer = c->drops && due == n_active && attention_plan(c).whole;
     const int candidates = c->max_candidates_due();
     ra::DueList list;
     if (due <= ra::kDueList) {

@@ -16,7 +16,7 @@ CHRON, HOLE, PAGED = B.RA_LAYOUT_CHRONOLOGICAL, B.RA_LAYOUT_HOLE_FILL, B.RA_LAYO
 
 
 @pytest.mark.parametrize("n,Hkv,lo,hi,rows,layout,splits", [
-    (33, 8, 20, 20, 3072, CHRON, 2),      # an event's moves cannot ride a halved head's step
+    (33, 8, 20, 20, 3072, CHRON, 2),      # the event's moves ride a step of whole heads
     (33, 8, 20, 20, 3071, CHRON, 1),
     (65, 4, 0, 150, 3300, PAGED, 2),
     (48, 8, 31, 31, 3100, HOLE, 2),       # 384 heads

@@ -70,3 +70,14 @@ def test_heads_halved_while_all_items_are_resident(plans, n, kv_heads, layout, s
     """Two items per head up to 384 heads: three workgroups fit a CU."""
     a = plans([3200] * n, layout=layout, kv_heads=kv_heads)[0]
     assert (a["waves"], a["splits"], a["wide"]) == (4, splits, 0)
+
+
+@pytest.mark.parametrize("n,prompt", [(48, 3200), (64, 3200), (33, 2000)])
+def test_lockstep_events_leave_their_moves_to_the_next_step(plans, n, prompt):
+    """Halved heads defer as whole ones do: the step after an event of every
+    sequence moves the rows, one workgroup per head, and the next is halved again."""
+    a = plans([prompt] * n, budget=64, recent=16, every=16, forward=95, steps=3)
+    assert [x["evicted"] for x in a] == [n, 0, 0]
+    assert [x["pending"] for x in a] == [1, 0, 0]
+    halves = 2 if n == 48 else 1
+    assert [(x["move"], x["splits"]) for x in a] == [(0, halves), (1, 1), (0, halves)]
