@@ -641,9 +641,7 @@ __global__ __launch_bounds__(NT) void move_pending_kernel(
 // One workgroup moves a head at 22 GB/s each way however idle the chip: an
 // event of 20 heads of 9,300 rows took 243 us on 20 CUs.  With a workgroup per
 // 512 rows it takes 24 us for the selection and 55 for the moves (3.5 TB/s of
-// reads and writes; 28 us for 10 heads); 64 paged heads of 3,100 rows: 12 + 53
-// us, 86 before.
-constexpr int kMaxChunks = 21;
+// reads and writes; 28 us for 10 heads).  event_chunks draws the line.
 struct ChunkLoaded {
   uint32_t* word;
   int chunk;
@@ -783,19 +781,9 @@ hipError_t launch_mode(const Shape& sh, const SeqMeta* meta, void* kpool,
   return hipErrorInvalidValue;
 }
 
-// Workgroups per head of a split move (0: one workgroup selects and moves a
-// head).  Split when the due heads leave half of the CUs idle: with more heads, the moves keep HBM busy anyway and the selections overlap them
-// (128 paged heads: 12 + 87 us split, 100 us in one launch; 64: 65 and 86).
-// A head's moved rows lie in [prompt, prompt + candidates + recent rows).
-int move_chunks(const Shape& sh, int max_candidates) {
-  if (!sh.move_sync || !sh.due || sh.due->n == 0 || sh.layout == 1) return 0;
-  const int64_t heads = static_cast<int64_t>(sh.due->n) * sh.L * sh.Hkv;
-  if (heads >= 128 || heads > sh.move_words) return 0;
-  const int chunk = sh.dtype == 1 ? chunk_rows<1024, uint16_t>() : chunk_rows<1024, float>();
-  if (sh.every + 8 > chunk) return 0;    // an event drops up to `every` rows
-  const int n = (max_candidates + sh.r + 7 + chunk - 1) / chunk;
-  return n >= 2 && n <= kMaxChunks ? n : 0;
-}
+static_assert(chunk_rows<1024, uint16_t>() == event_chunk_rows(1) &&
+                  chunk_rows<1024, float>() == event_chunk_rows(0),
+              "event_chunks counts the kernel's chunks");
 
 template <typename E, bool PAGED>
 void launch_chunks(const Shape& sh, const SeqMeta* meta, void* kpool, void* vpool,
@@ -860,7 +848,7 @@ hipError_t launch_evict(const Shape& sh, const SeqMeta* meta, void* kpool,
                         int max_candidates, bool positions_only,
                         hipStream_t s, int32_t* drops_out, int drop_stride) {
   if (slot_hi <= slot_lo) return hipSuccess;
-  const int n_chunks = positions_only ? 0 : move_chunks(sh, max_candidates);
+  const int n_chunks = positions_only ? 0 : event_chunks(sh, max_candidates);
   if (n_chunks > 0) {
     const hipError_t e = launch_mode<true>(sh, meta, kpool, vpool, pos, slot_lo, slot_hi,
                                            max_candidates, s, nullptr, 0, true);

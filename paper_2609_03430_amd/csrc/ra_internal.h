@@ -126,6 +126,32 @@ hipError_t launch_evict(const Shape& sh, const SeqMeta* meta, void* kpool,
                         void* vpool, int32_t* pos, int slot_lo, int slot_hi,
                         int max_candidates, bool positions_only, hipStream_t s,
                         int32_t* drops_out = nullptr, int drop_stride = 0);
+// Workgroups per head of a full event's moves: one per chunk of rows, launched
+// after the selection (0: the workgroup that selects a head moves it, in one
+// launch).  A head's moved rows lie in [prompt, prompt + candidates + recent).
+constexpr int event_chunk_rows(int dtype) { return dtype == 1 ? 512 : 256; }
+constexpr int kMaxChunks = 21;   // bits of a head's sync word left for its chunks
+inline int event_chunks(const Shape& sh, int max_candidates) {
+  if (!sh.move_sync || !sh.due || sh.due->n == 0 || sh.layout == 1) return 0;
+  const int64_t heads = static_cast<int64_t>(sh.due->n) * sh.L * sh.Hkv;
+  const int chunk = event_chunk_rows(sh.dtype);
+  // rows move down by less than a chunk: an event drops up to `every` rows
+  if (heads > sh.move_words || sh.every + 8 > chunk) return 0;
+  // Two launches and the hand-over between the workgroups against one launch:
+  // the second chunk has to be most of one (microseconds per event of 8 to 32
+  // bf16 heads: 578 rows 25 to 26 in one launch, 28 to 30 split; 846: 28 to 30 and 29
+  // to 30; 996: 30 and 28 to 30; 1,296: 36 and 30 to 33; 9,100: 222 and 118), and more
+  // than 64 heads keep HBM busy by themselves: split, all their workgroups have to
+  // run at once, one to a CU (96 heads: 996 rows 37 and 36, 1,296 rows 45 and 50,
+  // 4,100 paged 136 and 140; 120 heads, 1,900 rows: 68 and 71; 64: 58 and 46).
+  // fp32 chunks are half as long and a head's take longer: 120 heads of 1,300 rows
+  // 93 and 88, of 1,050 80 and 83.
+  const int64_t moved = static_cast<int64_t>(max_candidates) + sh.r;
+  const int n = static_cast<int>((moved + 7 + chunk - 1) / chunk);
+  if (4 * moved <= 7 * chunk || n > kMaxChunks) return 0;
+  const bool few = heads <= 64 || heads * n <= 256;
+  return few || (heads < 128 && sh.dtype == 0 && n >= 6) ? n : 0;
+}
 // n_steps steps of the active slots of [lo, hi), positions only, events
 // included (the chronological layouts, a trigger period, and at most `rows`
 // <= kMaxFastForwardRows generated rows per head at any time); the slot

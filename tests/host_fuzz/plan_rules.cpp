@@ -15,6 +15,7 @@
 
 extern "C" void stub_configure(int64_t pool_rows, int64_t n_groups, int max_seqs, int page_rows);
 extern ra::AttnLaunch g_attention;
+extern int g_event_chunks;
 
 #define CHECK(x)                                                          \
   do {                                                                    \
@@ -66,9 +67,9 @@ int main(int argc, char** argv) {
     ra_seq_info info;
     CHECK(ra_get_seq_info(cache, 0, &info));
     std::printf("{\"waves\":%d,\"wide\":%d,\"short\":%d,\"keys\":%d,\"splits\":%d,\"move\":%d,"
-                "\"evicted\":%d,\"pending\":%d,\"len\":%d}\n",
+                "\"evicted\":%d,\"pending\":%d,\"len\":%d,\"chunks\":%d}\n",
                 a.waves, a.wide_regs, a.short_runs, a.split_keys, a.max_splits, a.move, evicted,
-                info.move_pending, info.len);
+                info.move_pending, info.len, g_event_chunks);
   }
   CHECK(ra_cache_destroy(cache));
   return 0;

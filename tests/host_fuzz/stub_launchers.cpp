@@ -128,6 +128,8 @@ extern "C" int stub_check_tables(const int* active, const int* caps, int n) {
 
 // The last attention launch of the process, for the tests of the launch plan.
 ra::AttnLaunch g_attention;
+// and how its last event moves rows (event_chunks; -1: positions only)
+int g_event_chunks = 0;
 
 extern "C" hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes,
                                      hipMemcpyKind, hipStream_t) {
@@ -187,8 +189,9 @@ void check_chunk(const Shape& sh, int slot_lo, int slot_hi, const char* what) {
 }
 
 hipError_t launch_evict(const Shape& sh, const SeqMeta* meta, void*, void*, int32_t*, int slot_lo,
-                        int slot_hi, int max_candidates, bool, hipStream_t, int32_t* drops_out,
-                        int drop_stride) {
+                        int slot_hi, int max_candidates, bool positions_only, hipStream_t,
+                        int32_t* drops_out, int drop_stride) {
+  g_event_chunks = positions_only ? -1 : event_chunks(sh, max_candidates);
   if (slot_lo < 0 || slot_hi > g_max_seqs || slot_lo >= slot_hi) fail("evict range", slot_lo, slot_hi);
   check_chunk(sh, slot_lo, slot_hi, "evict launch over the per-launch bound");
   if (max_candidates < 0 || max_candidates > kMaxCandidates) fail("candidates", max_candidates, 0);

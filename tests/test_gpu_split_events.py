@@ -2,8 +2,9 @@
 
 Sequences on their own eviction phases, so that an event concerns one or two
 of them; budgets whose moved rows are a little less, exactly and a little more
-than a whole number of chunks (512 rows of bf16, 256 of fp32), and drop lists
-up to the longest that a chunk may have.  After every event the kept sets and
+than a whole number of chunks (512 rows of bf16, 256 of fp32), or than the 896
+rows from which bf16 moves split, and drop lists up to the longest that a chunk
+may have.  After every event the kept sets and
 rows equal the oracle's, and the counters that order the moves are zero.
 """
 
@@ -18,6 +19,7 @@ pytestmark = pytest.mark.gpu
 # (dtype, layout, layers, KV heads, K, r, every, prompts)
 CASES = [
     (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 1, 2, 505, 0, 16, [3, 40]),
+    (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 1, 2, 890, 0, 16, [3, 40]),     # first event whole
     (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 2, 2, 1024, 64, 64, [0, 17, 130]),
     (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 1, 4, 9000, 64, 64, [7, 1000]),
     (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 1, 1, 1500, 20, 500, [9, 100]),
