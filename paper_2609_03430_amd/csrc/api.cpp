@@ -1049,14 +1049,13 @@ ra_status ra_evict_now(ra_cache* c, int32_t seq, void* stream) {
 
 namespace {
 
-// Whether a fast forward runs as one launch (evict.hip): where it holds an
-// event (one event of 8 heads, 256 candidates: 9.8 us in one launch, 20 in three;
-// of 288 heads, 8,256 candidates: 50 and 57; eight events: 36 and 97, 316 and 420;
-// steps without one only
-// append), and not for hole-fill, whose positions are in no order, or caches over
-// the rows that the kernel keeps.  Paged: one sequence, whose page groups a shrink
-// returns and a growth takes again in the same order, so that its table holds
-// throughout.
+// Whether a fast forward runs as one launch (evict.hip): where it holds an event
+// (one of 8 heads, 364 candidates: 9.4 us in one launch, 17 in three; of 288 heads,
+// 8,964 candidates: 52 and 55; eight: 40 and 88, 314 and 424; steps without one
+// only append), and not for hole-fill, whose positions are in no order, or caches
+// over the rows that the kernel keeps.  Paged: one sequence, whose page groups a
+// shrink returns and a growth takes again in the same order, so that its table
+// holds throughout.
 bool fast_forward_fused(const ra_cache* c, int lo, int hi, int events, int64_t rows) {
   if (events == 0 || c->cfg.layout == RA_LAYOUT_HOLE_FILL || rows > ra::kMaxFastForwardRows)
     return false;

@@ -21,6 +21,8 @@
 //      hole-fill layout: only the surviving rows of the last m slots move,
 //      into the holes below the new length (order no longer chronological;
 //      the positions travel with the rows).
+#include <algorithm>
+
 #include "philox.h"
 #include "ra_internal.h"
 #include "select.h"
@@ -511,12 +513,14 @@ __global__ __launch_bounds__(NT) void evict_kernel(
 // the generated positions in LDS from the first step to the last.  The slot
 // records are read, not changed.
 //
-// Bound by the draws (the vector ALU).  Event by event, each took three
-// launches (new positions, slot records, selection) and a pass over the
+// Bound by the draws (the vector ALU), which every one of the NT * KPT keys
+// takes: the smallest build that holds the candidates.  Event by event, each took
+// three launches (new positions, slot records, selection) and a pass over the
 // positions in memory, and with more heads than CUs every selection waited for
 // the last head of the one before: 1,024-thread workgroups run one to a CU.
-// 512 threads with twice the keys each run two, up to 3,072 rows.  96 events of 288 heads,
-// 2,112 candidates: 2.18 -> 1.36 ms.
+// 512 threads with twice the keys each run two, up to 4,096 keys (288 heads, four
+// events of 3,000 candidates: 61 us; 86 with 1,024 x 4 keys).  96 events of 288
+// heads, 2,112 candidates: 1.98 -> 1.11 ms.
 template <int NT, int KPT, bool PAGED>
 __global__ __launch_bounds__(NT, 4) void fast_forward_kernel(
     const SeqMeta* __restrict__ meta, int32_t* __restrict__ pos, int Hkv, int per_seq, int r,
@@ -553,6 +557,9 @@ __global__ __launch_bounds__(NT, 4) void fast_forward_kernel(
       score[i] = 0;
       if (c < n && static_cast<int>(tie[i]) < thr) valid |= 1u << i;
     }
+    // rows past the keys are among the r most recent: they only move down
+    const bool moves = NT * KPT + t < n;
+    const int32_t recent = moves ? kept[NT * KPT + t] : 0;
     draw_keys<KPT>(score, tie, valid, policy, block, lp, event, layer, g, seed, rid);
     const uint32_t drop = select_smallest<NT, KPT, 64>(score, tie, valid, m, sel_sh);
     // every position was read before the selection's barriers: a survivor goes
@@ -568,6 +575,7 @@ __global__ __launch_bounds__(NT, 4) void fast_forward_kernel(
       if ((drop >> i) & 1) ++k;
       else if (c < n) kept[c - k] = static_cast<int32_t>(tie[i]);
     }
+    if (moves) kept[NT * KPT + t - m] = recent;
     n -= m;
     ++event;
   }
@@ -815,15 +823,24 @@ void launch_ff(const Shape& sh, const SeqMeta* meta, int32_t* pos, int slot_lo, 
 hipError_t launch_fast_forward(const Shape& sh, const SeqMeta* meta, int32_t* pos, int slot_lo,
                                int slot_hi, int n_steps, int rows, hipStream_t s) {
   if (slot_hi <= slot_lo) return hipSuccess;
-  if (rows <= 512 * 2)
-    launch_ff<512, 2>(sh, meta, pos, slot_lo, slot_hi, n_steps, rows, s);
-  else if (rows <= 512 * 6)
-    launch_ff<512, 6>(sh, meta, pos, slot_lo, slot_hi, n_steps, rows, s);
-  else if (rows <= kMaxFastForwardRows)
-    launch_ff<1024, kMaxFastForwardRows / 1024>(sh, meta, pos, slot_lo, slot_hi, n_steps, rows,
-                                                s);
-  else
-    return hipErrorInvalidValue;
+  // a key for every candidate; up to one more row per thread, all among the r
+  // most recent
+#define RA_FF_LAUNCH(NT, KPT)                      \
+  if (rows <= NT * KPT + std::min(sh.r, NT))       \
+  launch_ff<NT, KPT>(sh, meta, pos, slot_lo, slot_hi, n_steps, rows, s)
+  RA_FF_LAUNCH(512, 2);
+  else RA_FF_LAUNCH(512, 3);
+  else RA_FF_LAUNCH(512, 4);
+  else RA_FF_LAUNCH(512, 5);
+  else RA_FF_LAUNCH(512, 6);
+  else RA_FF_LAUNCH(512, 7);
+  else RA_FF_LAUNCH(512, 8);
+  else RA_FF_LAUNCH(1024, 5);
+  else RA_FF_LAUNCH(1024, 6);
+  else RA_FF_LAUNCH(1024, 7);
+  else RA_FF_LAUNCH(1024, 9);
+  else return hipErrorInvalidValue;
+#undef RA_FF_LAUNCH
   return hipGetLastError();
 }
 

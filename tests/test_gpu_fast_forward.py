@@ -1,8 +1,10 @@
 """Fast forwards over several events, in one launch per call, against the oracle.
 
-The kernel keeps a head's generated positions in LDS: 1,024, 3,072 or 9,216 of
-them, by the most that any sequence holds on the way; above that, for hole-fill
-and for several paged sequences the events are launched one by one.  Every head
+The kernel keeps a head's generated positions in LDS, up to 9,216 of them, and a
+key for each in registers, 2 to 8 on 512 threads or 5 to 9 on 1,024, by the most
+rows that any sequence holds on the way; rows past the keys are among the most
+recent, one to a thread.  Above that, for hole-fill and for several paged
+sequences the events are launched one by one.  Every head
 must hold the oracle's positions, and later decode steps and events must agree.
 """
 
@@ -36,6 +38,14 @@ def _check(run, oracles):
     (2945, [64], 64, 64, CHRON, B.RA_POLICY_SHARED, 1),
     (9088, [31], 64, 64, PAGED, B.RA_POLICY_RANDOM, 1),            # 9,216
     (9089, [31], 64, 64, CHRON, B.RA_POLICY_RANDOM, 1),            # event by event
+    # the builds full to their last recent row, and one row more
+    (960, [130, 0], 64, 64, CHRON, B.RA_POLICY_RANDOM, 1), (961, [33], 64, 64, CHRON, B.RA_POLICY_RANDOM, 1),
+    (1472, [5], 64, 64, PAGED, B.RA_POLICY_SHARED, 1), (1985, [77], 64, 64, CHRON, B.RA_POLICY_BLOCK, 3),
+    (2496, [8], 64, 64, CHRON, B.RA_POLICY_RANDOM, 1), (3009, [1], 64, 64, PAGED, B.RA_POLICY_RANDOM, 1),
+    (3520, [64], 64, 64, CHRON, B.RA_POLICY_RECENCY, 1), (4032, [9], 64, 64, CHRON, B.RA_POLICY_RANDOM, 1),
+    (4033, [9], 64, 64, PAGED, B.RA_POLICY_RANDOM, 1), (5057, [2], 64, 64, CHRON, B.RA_POLICY_RANDOM, 1),
+    (6080, [40], 64, 64, CHRON, B.RA_POLICY_RANDOM, 1), (7105, [3], 64, 64, CHRON, B.RA_POLICY_RANDOM, 1),
+    (772, [20], 700, 64, CHRON, B.RA_POLICY_RANDOM, 1), (773, [20], 700, 64, CHRON, B.RA_POLICY_RANDOM, 1),
     (100, [12, 90], 16, 16, CHRON, B.RA_POLICY_BLOCK, 4),
     (100, [12, 90], 50, 16, CHRON, B.RA_POLICY_RECENCY, 1),
     (300, [50, 80], 33, 64, PAGED, B.RA_POLICY_RANDOM, 1),         # two paged sequences
