@@ -19,14 +19,15 @@
 // Bound by the vector work per logit (a fused multiply-add, an exponential at
 // a quarter of the rate, an addition), which the matrix products of the other
 // wavefronts of a SIMD run beside: a head has one workgroup, so it fills all
-// four wavefronts of every SIMD (128 registers each: two query tiles; three
-// spill).  They divide the query tiles and, where these are few, the keys of a
+// four wavefronts of every SIMD (128 registers each, none spilled: two query
+// tiles; what the loops do not need is derived again where it is used).
+// They divide the query tiles and, where these are few, the keys of a
 // block between them, so that a key tile read from LDS serves two query tiles
 // (one: the LDS reads take longer than the logits).
 // Pass 1 keeps its reference as long as no logit passes it by more than 2^8,
 // instead of raising it in every block.  240 heads of 9,376 rows,
-// G = 4: 607 -> 440 to 457 us (G = 1: 240 -> 148 at 192 heads of 4,900 rows, G = 8: 466 ->
-// 404, G = 16, whose operands spilled: 4.4 -> 0.67 ms).
+// G = 4: 575 -> 449 us (G = 1: 220 -> 133 at 192 heads of 4,890 rows, G = 8: 414 ->
+// 354; G = 16, 24 heads, whose operands spilled: 4.1 -> 0.63 ms).
 #include <type_traits>
 
 #include "ra_internal.h"
@@ -39,9 +40,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kNT = 1024;
-constexpr int kWaves = kNT / 64;
-constexpr int kBlk = 128;         // key rows per LDS block
+// Key rows per LDS block of a workgroup of NT threads.
+template <int NT>
+constexpr int kBlk = NT / 8;
 constexpr int kWin = 64;          // window queries per query head
 constexpr int kRowStride = 136;   // bf16 elements per LDS row (256 B + 16 B pad)
 constexpr int kTilesPerWave = 2;  // query tiles a wavefront holds in registers
@@ -58,16 +59,17 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
   return r;
 }
 
-// LDS of a workgroup besides the scores: 87 KB, beside which the scores of the
-// longest cache (16,384 rows) take 64 of the 160 KB.  The sums of a block are
-// read while the next block's are written.
+// LDS of a workgroup besides the scores: 87 KB for 1,024 threads, beside which
+// the scores of the longest cache (16,384 rows) take 64 of the 160 KB. The sums of a block are read while the next block's are written.
+template <int NT>
 struct Lds {
+  static constexpr int kWaves = NT / 64;
   union {
     struct {
-      uint16_t k[2][kBlk * kRowStride];
-      int pos[2][kBlk];
+      uint16_t k[2][kBlk<NT> * kRowStride];
+      int pos[2][kBlk<NT>];
       union {
-        float sums[2][kWaves][kBlk];             // [.][query group][key]
+        float sums[2][kWaves][kBlk<NT>];         // [.][query group][key]
         struct {
           float off[kWaves][16], sum[kWaves][16];   // one tile of every wavefront
         } merge;
@@ -80,56 +82,67 @@ struct Lds {
   };
 };
 
+// A value that the compiler takes as new: what it derives from it is computed
+// where it is used, not kept in registers through the loops.
+__device__ __forceinline__ int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+constexpr int kPieces = 2;
+static_assert(kBlk<1024> * 16 == kPieces * 1024, "a block is two pieces per thread");
 struct KBlock {
-  u32x4 u[kBlk * 16 / kNT];   // this thread's 16-byte pieces of a block
-  int p;               // position of row t (threads < kBlk)
+  u32x4 u[kPieces];    // this thread's 16-byte pieces of a block
+  int p;               // position of row t (the first threads)
 };
 
+template <int NT>
 __device__ __forceinline__ void fetch_block(KBlock& b, const uint16_t* Kr,
                                             const int32_t* P, int kb, int len) {
-  const int t = threadIdx.x;
+  const int t = fresh(threadIdx.x);
   const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int q = 0; q < kBlk * 16 / kNT; ++q) {
-    const int piece = t + q * kNT;          // 16 pieces of 16 bytes to a row
+  for (int q = 0; q < kPieces; ++q) {
+    const int piece = t + q * NT;          // 16 pieces of 16 bytes to a row
     const int row = piece >> 4, col = piece & 15;
     b.u[q] = (kb + row < len)
         ? *reinterpret_cast<const u32x4*>(Kr + static_cast<int64_t>(kb + row) * kHeadDim + col * 8)
         : z;
   }
-  b.p = (t < kBlk && kb + t < len) ? P[kb + t] : 0x7fffffff;
+  b.p = (t < kBlk<NT> && kb + t < len) ? P[kb + t] : 0x7fffffff;
 }
 
+template <int NT>
 __device__ __forceinline__ void store_block(const KBlock& b, uint16_t* lk, int* lpos) {
-  const int t = threadIdx.x;
+  const int t = fresh(threadIdx.x);
 #pragma unroll
-  for (int q = 0; q < kBlk * 16 / kNT; ++q) {
-    const int piece = t + q * kNT;
+  for (int q = 0; q < kPieces; ++q) {
+    const int piece = t + q * NT;
     const int row = piece >> 4, col = piece & 15;
     *reinterpret_cast<u32x4*>(lk + row * kRowStride + col * 8) = b.u[q];
   }
-  if (t < kBlk) lpos[t] = b.p;
+  if (t < kBlk<NT>) lpos[t] = b.p;
 }
 
 // Stream the head's cached rows through LDS (the next block prefetched into
 // registers while the current one is used) and call body(b, keys, positions)
 // once per block, with the whole workgroup.
-template <typename Body>
+template <int NT, typename Body>
 __device__ __forceinline__ void stream_blocks(const uint16_t* Kr, const int32_t* P, int len,
-                                              Lds& lds, Body body) {
+                                              Lds<NT>& lds, Body body) {
   auto& st = lds.stream;
-  const int nblk = (len + kBlk - 1) / kBlk;
+  const int nblk = (len + kBlk<NT> - 1) / kBlk<NT>;
   KBlock nb;
-  fetch_block(nb, Kr, P, 0, len);
+  fetch_block<NT>(nb, Kr, P, 0, len);
   __syncthreads();                 // the previous user of the buffers is done with them
-  store_block(nb, st.k[0], st.pos[0]);
+  store_block<NT>(nb, st.k[0], st.pos[0]);
   __syncthreads();
   for (int b = 0; b < nblk; ++b) {
     const int cur = b & 1;
-    if (b + 1 < nblk) fetch_block(nb, Kr, P, (b + 1) * kBlk, len);
+    if (b + 1 < nblk) fetch_block<NT>(nb, Kr, P, (b + 1) * kBlk<NT>, len);
     body(b, st.k[cur], st.pos[cur]);
     // the other buffer was last read before the previous barrier
-    if (b + 1 < nblk) store_block(nb, st.k[cur ^ 1], st.pos[cur ^ 1]);
+    if (b + 1 < nblk) store_block<NT>(nb, st.k[cur ^ 1], st.pos[cur ^ 1]);
     __syncthreads();
   }
 }
@@ -166,16 +179,17 @@ __device__ __forceinline__ void score_tiles(f32x4 (&x)[2][N],
         x[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qop[j][s], kop[h][s], x[h][j], 0, 0, 0);
 }
 
-template <int KPT>
-__global__ __launch_bounds__(kNT) void window_score_kernel(
+template <int NT, int KPT>
+__global__ __launch_bounds__(NT, 4) void window_score_kernel(
     const SeqMeta* __restrict__ meta, const uint16_t* __restrict__ kpool,
     const int32_t* __restrict__ pos, const uint16_t* __restrict__ qwin,
     float* __restrict__ scores_out, int32_t* __restrict__ drops_out,
     int scores_stride, int L, int Hq, int Hkv, int G, int r, int every,
     int slot_lo, float scale_log2) {
+  constexpr int kWaves = NT / 64;
   extern __shared__ __align__(16) char smem[];
-  Lds& lds = *reinterpret_cast<Lds*>(smem);
-  float* score = reinterpret_cast<float*>(smem + sizeof(Lds));   // [len]
+  Lds<NT>& lds = *reinterpret_cast<Lds<NT>*>(smem);
+  float* score = reinterpret_cast<float*>(smem + sizeof(Lds<NT>));   // [len]
 
   const int per_seq = L * Hkv;
   const int slot = slot_lo + static_cast<int>(blockIdx.x) / per_seq;
@@ -192,7 +206,7 @@ __global__ __launch_bounds__(kNT) void window_score_kernel(
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int qi = lane & 15, grp = lane >> 4;
-  for (int i = t; i < len; i += kNT) score[i] = 0.f;
+  for (int i = t; i < len; i += NT) score[i] = 0.f;
 
   const int first_pos = lp + M.step - kWin;     // position of window row 0
   const int n_tiles = G * 4;
@@ -206,7 +220,7 @@ __global__ __launch_bounds__(kNT) void window_score_kernel(
     int qgroups = 4;
     while (qgroups * kTilesPerWave < round) qgroups *= 2;
     const int qg = wave % qgroups;
-    const int tiles = kBlk / 16 * qgroups / kWaves, kt0 = wave / qgroups * tiles;
+    const int tiles = kBlk<NT> / 16 * qgroups / kWaves, kt0 = wave / qgroups * tiles;
     // this wavefront's query tiles: qt = tile0 + j * qgroups + qg for j < ntile
     // (round robin, so that they spread evenly over the SIMDs; one or two, as
     // a round has at least qgroups tiles); tile qt covers head qt / 4, window
@@ -247,7 +261,7 @@ __global__ __launch_bounds__(kNT) void window_score_kernel(
       }
     auto pass1_block = [&](const uint16_t* lkb, const int* lpb, auto count) {
       constexpr int kTiles = decltype(count)::value;
-      const bool masked = lpb[kBlk - 1] > first_pos;
+      const bool masked = lpb[kBlk<NT> - 1] > first_pos;
       for (int kt = kt0; kt < kt0 + tiles; kt += 2) {
         f32x4 x[2][kTiles];
         score_tiles(x, qop, lkb, kt, qi, grp);
@@ -358,13 +372,14 @@ __global__ __launch_bounds__(kNT) void window_score_kernel(
         const bool odd = grp & 1;
         float c = (odd ? colsum[1] : colsum[0]) + __shfl_xor(odd ? colsum[0] : colsum[1], 16, 64);
         c += __shfl_xor(c, 32, 64);
-        if (grp < 2) out[(kt + grp) * 16 + qi] = c;
+        const int l = fresh(threadIdx.x) & 63;    // grp * 16 + qi
+        if (l < 32) out[kt * 16 + l] = c;
       }
     };
     // the sums of block b over the query groups, in their order
     auto add_block = [&](int b) {
-      const int key = b * kBlk + t;
-      if (t < kBlk && key < len) {
+      const int t = fresh(threadIdx.x), key = b * kBlk<NT> + t;
+      if (t < kBlk<NT> && key < len) {
         float s = score[key];
         for (int w = 0; w < qgroups; ++w) s += lds.stream.sums[b % 2][w][t];
         score[key] = s;
@@ -374,17 +389,17 @@ __global__ __launch_bounds__(kNT) void window_score_kernel(
       if (b > 0) add_block(b - 1);
       float* out = lds.stream.sums[b % 2][qg];
       by_tiles([&](auto count) {
-        if (lpb[kBlk - 1] > first_pos) pass2_tiles(lkb, lpb, out, count, std::true_type{});
+        if (lpb[kBlk<NT> - 1] > first_pos) pass2_tiles(lkb, lpb, out, count, std::true_type{});
         else pass2_tiles(lkb, lpb, out, count, std::false_type{});
       });
     });
-    add_block((len - 1) / kBlk);
+    add_block((len - 1) / kBlk<NT>);
   }
   __syncthreads();
 
   const int64_t head_out = static_cast<int64_t>(slot - slot_lo) * per_seq + lg;
   if (scores_out) {
-    for (int i = t; i < len; i += kNT) scores_out[head_out * scores_stride + i] = score[i];
+    for (int i = t; i < len; i += NT) scores_out[head_out * scores_stride + i] = score[i];
   }
   if (!drops_out || m <= 0) return;
   // max-pool and select the m lowest candidates
@@ -404,10 +419,10 @@ __global__ __launch_bounds__(kNT) void window_score_kernel(
       valid |= 1u << i;
     }
   }
-  const uint32_t drop = select_smallest<kNT, KPT, 32>(key, tie, valid, m, lds.pick.sel);
+  const uint32_t drop = select_smallest<NT, KPT, 32>(key, tie, valid, m, lds.pick.sel);
   int* f = lds.pick.f;
-  drop_list<kNT, KPT>(drop, 0, f, lds.pick.sel);
-  for (int k = t; k < m; k += kNT) drops_out[head_out * every + k] = f[k] + k;
+  drop_list<NT, KPT>(drop, 0, f, lds.pick.sel);
+  for (int k = t; k < m; k += NT) drops_out[head_out * every + k] = f[k] + k;
 }
 
 }  // namespace
@@ -422,14 +437,14 @@ hipError_t launch_window_score(const Shape& sh, const SeqMeta* meta, const void*
   const uint16_t* k = static_cast<const uint16_t*>(kpool);
   const uint16_t* q = static_cast<const uint16_t*>(qwin);
   const int n_cand = max_len;   // upper bound of len - r
-  const size_t shmem = sizeof(Lds) + sizeof(float) * static_cast<size_t>(max_len);
-#define RA_WS_LAUNCH(K)                                                                    \
-  hipLaunchKernelGGL((window_score_kernel<K>), grid, dim3(kNT), shmem, s, meta, k, pos, q, \
-                     scores_out, drops_out, scores_stride, sh.L, sh.Hq, sh.Hkv, sh.G,      \
-                     sh.r, sh.every, slot_lo, scale)
-  if (n_cand <= kNT * 4) RA_WS_LAUNCH(4);
-  else if (n_cand <= kNT * 8) RA_WS_LAUNCH(8);
-  else if (n_cand <= kNT * 16) RA_WS_LAUNCH(16);
+  const auto shmem = [&](size_t fixed) { return fixed + sizeof(float) * static_cast<size_t>(max_len); };
+#define RA_WS_LAUNCH(NT, K)                                                                \
+  hipLaunchKernelGGL((window_score_kernel<NT, K>), grid, dim3(NT), shmem(sizeof(Lds<NT>)), s, \
+                     meta, k, pos, q, scores_out, drops_out, scores_stride, sh.L, sh.Hq,   \
+                     sh.Hkv, sh.G, sh.r, sh.every, slot_lo, scale)
+  if (n_cand <= 1024 * 4) RA_WS_LAUNCH(1024, 4);
+  else if (n_cand <= 1024 * 8) RA_WS_LAUNCH(1024, 8);
+  else if (n_cand <= 1024 * 16) RA_WS_LAUNCH(1024, 16);
   else return hipErrorInvalidValue;
 #undef RA_WS_LAUNCH
   return hipGetLastError();

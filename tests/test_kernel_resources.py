@@ -5,10 +5,11 @@ registers for the 12-wavefront attention workgroup, whose three wavefronts
 per SIMD share 512; 128 for the 1,024-thread eviction workgroup): a change in an
 address expression can make the compiler spill to scratch memory in the
 inner loop, which costs 5-10% of their bandwidth.  This test compiles the
-attention, eviction and state kernels for gfx950 (device code only, to AMD
-assembly) and checks that no build spills vector registers.  The eviction
-build that holds 32 keys per thread keeps its key array in scratch memory
-by design (the largest selections only); it is not a spill.
+kernels for gfx950 (device code only, to AMD assembly) and checks that no
+build spills vector registers.  The eviction build that holds 32 keys per
+thread keeps its key array in scratch memory by design (the largest
+selections only); it is not a spill.  One build of the VaSE diagnostic (4,097
+to 8,192 rows) spills around its selection, within the bound below.
 """
 
 import json
@@ -25,7 +26,7 @@ CSRC = os.path.join(ROOT, "paper_2609_03430_amd", "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 RECORD = os.path.join(ROOT, "_build", "kernel_resources.json")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-SOURCES = ["attention.hip", "evict.hip", "state.hip"]
+ACCEPTED = {"vase_kernelILi16E": 1792}
 
 
 def _compile_spills(src):
@@ -66,12 +67,11 @@ def _spills(src):
 
 @pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which(HIPCC) is None,
                     reason="hipcc not available")
-@pytest.mark.parametrize("src,kernel", [("attention.hip", "attn_"),
-                                        ("evict.hip", "evict_kernel"),
-                                        ("state.hip", "")])
-def test_no_register_spills(src, kernel):
+@pytest.mark.parametrize("src", ["attention.hip", "evict.hip", "state.hip", "window_score.hip",
+                                 "scored.hip"])
+def test_no_register_spills(src):
     spills = _spills(src)
-    mine = {k: v for k, v in spills.items() if kernel in k}
-    assert mine, "no kernels found in " + src
-    bad = {k: v for k, v in mine.items() if v}
+    assert spills, "no kernels found in " + src
+    bad = {k: v for k, v in spills.items()
+           if v > next((n for name, n in ACCEPTED.items() if name in k), 0)}
     assert not bad, bad
