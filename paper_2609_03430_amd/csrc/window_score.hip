@@ -5,7 +5,7 @@
 // position as the sum of the attention weights of the last w queries,
 // max-pooled over neighbouring positions; Eq. 1 keeps the top-scoring
 // candidates (cached rows outside the r most recent).  Per (sequence, layer,
-// KV head), one 1,024-thread workgroup:
+// KV head), one workgroup of 1,024 or 512 threads:
 //   pass 1: for every window query (G heads x 64 steps) the softmax reference
 //           and sum of q.k/sqrt(d) over the cached rows at or before its
 //           position;
@@ -60,7 +60,8 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
 }
 
 // LDS of a workgroup besides the scores: 87 KB for 1,024 threads, beside which
-// the scores of the longest cache (16,384 rows) take 64 of the 160 KB. The sums of a block are read while the next block's are written.
+// the scores of the longest cache (16,384 rows) take 64 of the 160 KB; 39 KB for
+// 512.  The sums of a block are read while the next block's are written.
 template <int NT>
 struct Lds {
   static constexpr int kWaves = NT / 64;
@@ -442,7 +443,15 @@ hipError_t launch_window_score(const Shape& sh, const SeqMeta* meta, const void*
   hipLaunchKernelGGL((window_score_kernel<NT, K>), grid, dim3(NT), shmem(sizeof(Lds<NT>)), s, \
                      meta, k, pos, q, scores_out, drops_out, scores_stride, sh.L, sh.Hq,   \
                      sh.Hkv, sh.G, sh.r, sh.every, slot_lo, scale)
-  if (n_cand <= 1024 * 4) RA_WS_LAUNCH(1024, 4);
+  // More heads than CUs, short caches: two workgroups of 512 threads to a CU
+  // overlap their prologues, barriers and selections, where those of 1,024 run one
+  // by one (1,024 and 512 threads, us at G = 4: 264 heads of 490 rows 82 and 60, of
+  // 1,190 135 and 111, of 2,690 244 and 220, of 4,090 336 and 316; 512 heads of 4,090
+  // alike; 256 heads of 1,190 77 and 78, of 2,690 135 and 153).  Above G = 4 they
+  // would read the keys a second time.
+  if (grid.x > 256 && sh.G <= 4 && n_cand <= 512 * 4) RA_WS_LAUNCH(512, 4);
+  else if (grid.x > 256 && sh.G <= 4 && n_cand <= 512 * 8) RA_WS_LAUNCH(512, 8);
+  else if (n_cand <= 1024 * 4) RA_WS_LAUNCH(1024, 4);
   else if (n_cand <= 1024 * 8) RA_WS_LAUNCH(1024, 8);
   else if (n_cand <= 1024 * 16) RA_WS_LAUNCH(1024, 16);
   else return hipErrorInvalidValue;

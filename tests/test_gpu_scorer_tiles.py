@@ -2,8 +2,8 @@
 
 The window scorer divides a head's 4 G query tiles and the keys of a block
 between its wavefronts by G, with two rounds of query tiles above G = 8: the
-groups below take every split between the ones other tests take.  R-KV's
-similarities run over 512-row chunks against 64-column blocks, the chunks of a
+groups below take every split between the ones other tests take.  More than 256 heads of a short cache take workgroups of 512 threads.
+R-KV's similarities run over 512-row chunks against 128-column blocks, the chunks of a
 head on one die of eight: several chunks, a ragged last column tile, and
 near-duplicates inside a row's own tile, across tiles and across chunks.
 """
@@ -32,6 +32,27 @@ def test_window_query_groups(G, K, steps):
         for o in oracles:
             o.rep.append()
     _select_and_check(run, oracles, min(steps, K + 63 + 25), stride=512)
+    run.close()
+
+
+@pytest.mark.parametrize("Hkv,G,K", [
+    (129, 4, 40), (129, 1, 41), (129, 3, 1840), (129, 2, 1900), (129, 5, 60), (128, 2, 40)])
+def test_window_many_heads(Hkv, G, K):
+    """258 heads (512 threads; G = 5 not) and 256; 2,048 rows and fewer take 4 candidates
+    per thread, more take 8."""
+    log("window scorer Hkv=%d G=%d K=%d" % (Hkv, G, K))
+    steps = K + 63 + 33
+    run = Run(L=1, Hq=Hkv * G, Hkv=Hkv, K=K, lps=[90, 33], r=63, every=64,
+              policy=B.RA_POLICY_EXTERNAL)
+    run.fast_forward(steps)
+    oracles = [OracleSeq(run, s, heads=[(0, g) for g in (0, Hkv // 2, Hkv - 1)])
+               for s in range(run.n)]
+    for s in range(run.n):
+        run.materialise(s)
+    for o in oracles:
+        for _ in range(steps):
+            o.rep.append()
+    _select_and_check(run, oracles, steps, stride=2176)
     run.close()
 
 

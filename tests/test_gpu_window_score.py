@@ -63,35 +63,34 @@ def _select_and_check(run, oracles, n_steps, stride):
         n = info.len
         m = n - o.lp - r - run.k_keep(b)
         assert m > 0
-        for l in range(L):
-            for g in range(Hkv):
-                P = o.rep.P[(l, g)]
-                k, _ = o.rows(l, g, P)
-                q = o.wl.q_rows(o.rid, l, torch.arange(g * G, (g + 1) * G).view(-1, 1),
-                                torch.arange(n_steps - 64, n_steps).view(1, -1))
-                qpos = (o.lp + np.arange(n_steps - 64, n_steps))[None, :].repeat(G, 0)
-                want = window_scores(q.reshape(-1, 128).double().numpy(), qpos.reshape(-1),
-                                     k.double().numpy(), P)
-                got = scores[b, l, g, :n]
-                assert np.all(np.abs(got - want) <= 2e-3 + 1e-3 * np.abs(want)), (b, l, g)
-                pooled = max_pool(want, 7)[: n - r]
-                d = drops[b, l, g, :m]
-                assert np.all(np.diff(d) > 0) and d.min() >= 0 and d.max() < n - r
-                thr = np.sort(pooled)[m - 1]
-                tol = 4e-3 + 2e-3 * thr
-                kept = np.setdiff1d(np.arange(n - r), d)
-                assert np.all(pooled[d] <= thr + tol), (b, l, g)
-                assert np.all(pooled[kept] >= thr - tol), (b, l, g)
+        for l, g in o.heads:
+            P = o.rep.P[(l, g)]
+            k, _ = o.rows(l, g, P)
+            q = o.wl.q_rows(o.rid, l, torch.arange(g * G, (g + 1) * G).view(-1, 1),
+                            torch.arange(n_steps - 64, n_steps).view(1, -1))
+            qpos = (o.lp + np.arange(n_steps - 64, n_steps))[None, :].repeat(G, 0)
+            want = window_scores(q.reshape(-1, 128).double().numpy(), qpos.reshape(-1),
+                                 k.double().numpy(), P)
+            got = scores[b, l, g, :n]
+            assert np.all(np.abs(got - want) <= 2e-3 + 1e-3 * np.abs(want)), (b, l, g)
+            pooled = max_pool(want, 7)[: n - r]
+            d = drops[b, l, g, :m]
+            assert np.all(np.diff(d) > 0) and d.min() >= 0 and d.max() < n - r
+            thr = np.sort(pooled)[m - 1]
+            tol = 4e-3 + 2e-3 * thr
+            kept = np.setdiff1d(np.arange(n - r), d)
+            assert np.all(pooled[d] <= thr + tol), (b, l, g)
+            assert np.all(pooled[kept] >= thr - tol), (b, l, g)
 
 
 @pytest.mark.parametrize("K,lps,steps,Hq,Hkv", [
-    (4096, [1024, 300], 4190, 8, 2),       # 5,214 rows: the 16-keys-per-thread build
-    (8192, [2048, 100], 8300, 8, 2),       # 10,348 rows: the 32-keys-per-thread build
-    (8192, [2048, 100], 8300, 10, 2),      #   the same with G = 5 (three tiles per wave)
+    (4096, [1024, 300], 4190, 8, 2),       # 5,214 rows: the 8-keys-per-thread build
+    (8192, [2048, 100], 8300, 8, 2),       # 10,348 rows: the 16-keys-per-thread build
+    (8192, [2048, 100], 8300, 10, 2),      #   the same with G = 5 (tiles left over)
 ])
 def test_window_select_large_caches(K, lps, steps, Hq, Hkv):
     """Caches of the Phi-4-shaped batch's size (prompts up to 2,048, K = 8,192):
-    the selection holds 16 or 32 keys per thread.  The state is reached by a
+    the selection holds 8 or 16 keys per thread.  The state is reached by a
     positions-only fast forward to a step before the next trigger, so the
     rows over budget (steps - r - K) are fewer than evict_every, and the
     cached rows are materialised from the generator."""
