@@ -36,6 +36,9 @@ int g_max_seqs = 0;
 int g_page_rows = 0;
 const int32_t* g_tables = nullptr;
 int g_pps = 0;               // paged: table entries per sequence
+const char* g_meta = nullptr;   // the metadata buffer (zeroed when a cache is created)
+size_t g_meta_bytes = 0;
+std::vector<int> g_launched;    // events launched, per slot: the last one's number + 1
 
 // the allocation-free entry point's partials array (its real size)
 std::vector<char>& scratch_array() {
@@ -106,6 +109,7 @@ extern "C" void stub_configure(int64_t pool_rows, int64_t n_groups, int max_seqs
   g_page_rows = page_rows;
   g_tables = nullptr;
   g_pps = 0;
+  g_launched.assign(max_seqs, 0);
 }
 
 // Paged: the active sequences' first `caps[s] / page_rows` table entries are
@@ -142,6 +146,8 @@ extern "C" hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 namespace ra {
 
 hipError_t launch_zero_words(uint32_t* p, int64_t n_words, hipStream_t) {
+  g_meta = reinterpret_cast<const char*>(p);
+  g_meta_bytes = static_cast<size_t>(n_words) * 4;
   std::memset(p, 0, static_cast<size_t>(n_words) * 4);
   return hipSuccess;
 }
@@ -149,6 +155,7 @@ hipError_t launch_zero_words(uint32_t* p, int64_t n_words, hipStream_t) {
 hipError_t launch_seq_set(SeqMeta* meta, int slot, const SeqMeta& v, hipStream_t) {
   if (slot < 0 || slot >= g_max_seqs) fail("seq_set slot", slot, g_max_seqs);
   meta[slot] = v;
+  g_launched[slot] = 0;
   return hipSuccess;
 }
 
@@ -188,15 +195,62 @@ void check_chunk(const Shape& sh, int slot_lo, int slot_hi, const char* what) {
     fail(what, slot_lo, slot_hi);
 }
 
+// `bytes` bytes at p lie in the metadata buffer.
+void check_meta(const void* p, int64_t bytes, const char* what) {
+  const char* b = static_cast<const char*>(p);
+  if (bytes < 0 || b < g_meta || b + bytes > g_meta + g_meta_bytes) fail(what, b - g_meta, bytes);
+}
+
+// The event of a due slot: its candidates fit the launch, its old rows the pool.
+void check_event(const Shape& sh, const SeqMeta* meta, int slot, int max_candidates) {
+  SeqMeta M = meta[slot];
+  const int span = M.plan_len - M.prompt_len - (sh.layout == 1 ? 0 : sh.r);
+  if (span > max_candidates) fail("event candidates", span, max_candidates);
+  if (sh.layout == 2) M.cap = M.plan_len;   // the device's record keeps the capacity of the start
+  check_rows(sh, M, slot, M.plan_len);
+  g_launched[slot] = M.plan_event + 1;
+}
+
 hipError_t launch_evict(const Shape& sh, const SeqMeta* meta, void*, void*, int32_t*, int slot_lo,
                         int slot_hi, int max_candidates, bool positions_only, hipStream_t,
                         int32_t* drops_out, int drop_stride) {
   g_event_chunks = positions_only ? -1 : event_chunks(sh, max_candidates);
   if (slot_lo < 0 || slot_hi > g_max_seqs || slot_lo >= slot_hi) fail("evict range", slot_lo, slot_hi);
-  check_chunk(sh, slot_lo, slot_hi, "evict launch over the per-launch bound");
   if (max_candidates < 0 || max_candidates > kMaxCandidates) fail("candidates", max_candidates, 0);
-  if (drops_out && (drop_stride < 1 || drop_stride > kMaxEvery)) fail("drop stride", drop_stride, 0);
-  touch_read(meta + slot_lo, sizeof(SeqMeta) * (slot_hi - slot_lo));
+  const int64_t heads = static_cast<int64_t>(sh.L) * sh.Hkv;
+  if (drops_out) {
+    if (drop_stride < 1 || drop_stride > kMaxEvery) fail("drop stride", drop_stride, 0);
+    check_meta(drops_out, g_max_seqs * heads * drop_stride * 4, "drop lists outside the metadata");
+  }
+  if (!sh.due || sh.due->n == 0) {
+    check_chunk(sh, slot_lo, slot_hi, "evict launch over the per-launch bound");
+    for (int s = slot_lo; s < slot_hi; ++s)
+      if (meta[s].active && meta[s].due == 1) check_event(sh, meta, s, max_candidates);
+    return hipSuccess;
+  }
+  // listed slots: ascending, due, and with those launched before all that are due
+  const DueList& due = *sh.due;
+  if (due.n < 0 || due.n > kDueList || due.slot[0] != slot_lo) fail("due list", due.n, due.slot[0]);
+  if (due.n * heads > RA_MAX_HEADS_PER_LAUNCH) fail("listed event over the per-launch bound", due.n, heads);
+  for (int k = 0; k < due.n; ++k) {
+    const int s = due.slot[k];
+    if (s < 0 || s >= g_max_seqs || (k > 0 && s <= due.slot[k - 1])) fail("due slot", k, s);
+    if (!meta[s].active || meta[s].due != 1) fail("listed slot not due", k, s);
+    check_event(sh, meta, s, max_candidates);
+    // the split moves need moves of less than a chunk, and lists of `every` drops
+    if (sh.move_sync && meta[s].plan_len - meta[s].len > sh.every)
+      fail("event drops more than its period", meta[s].plan_len - meta[s].len, sh.every);
+  }
+  for (int s = 0; s < g_max_seqs; ++s)
+    if (meta[s].active && meta[s].due == 1 && g_launched[s] != meta[s].plan_event + 1)
+      fail("due slot not listed", s, due.n);
+  if (sh.move_sync) {
+    check_meta(sh.move_sync, sh.move_words * 4, "sync words outside the metadata");
+    for (int64_t w = 0; w < sh.move_words; ++w)
+      if (sh.move_sync[w]) fail("sync word in use", w, sh.move_sync[w]);
+    if (event_chunks(sh, max_candidates) > 0 && due.n * heads > sh.move_words)
+      fail("more heads than sync words", due.n * heads, sh.move_words);
+  }
   return hipSuccess;
 }
 
