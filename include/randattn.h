@@ -296,8 +296,8 @@ ra_status ra_get_seq_info(const ra_cache* cache, int32_t seq, ra_seq_info* out);
  * pool has too few free groups (ending a sequence frees its groups).  After
  * an event whose row moves were deferred (ra_end_step), the layer's
  * attention also moves that layer's surviving rows to their compacted slots
- * (if the step's plan splits a head into several work items, a separate
- * launch moves them first). */
+ * (if the step's plan splits a head into several work items, other than the
+ * halves of 257 to 384 heads, a separate launch moves them first). */
 ra_status ra_decode_attention(ra_cache* cache, int32_t layer, const void* q,
                               const void* k_new, const void* v_new, void* out,
                               void* workspace, size_t workspace_bytes,
@@ -312,8 +312,8 @@ ra_status ra_decode_attention(ra_cache* cache, int32_t layer, const void* q,
  * ra_cache_create).  The call allocates nothing and calls no allocating
  * routine.  It counts (slots up to the highest active one) * Hkv * S * G * 130
  * * 4 bytes of that array when S > 1 (always for f32), and returns
- * RA_ERR_CAPACITY,
- * before any launch, when that exceeds RA_NOALLOC_SCRATCH_BYTES.  Every call
+ * RA_ERR_CAPACITY, before any launch, when that exceeds
+ * RA_NOALLOC_SCRATCH_BYTES.  Every call
  * on one GPU shares the array, from any cache: calls that overlap on one GPU
  * (other streams, other threads) race on it and must be serialised by the
  * caller.  Nothing in the array needs to start at zero.  S: the work items
@@ -331,8 +331,9 @@ ra_status ra_decode_attention_noalloc(ra_cache* cache, int32_t layer, const void
  * trigger) on every (layer, KV head) of each sequence that is due (never
  * under RA_POLICY_EXTERNAL).  bf16, contiguous chronological layout: when
  * every active sequence is due at this step and the next step's attention
- * gives each head one work item, the event selects and compacts the
- * positions only, and that attention moves each layer's key/value rows while
+ * gives each head one work item (or halves each of 257 to 384 heads), the
+ * event selects and compacts the positions only, and that attention, one
+ * workgroup per head, moves each layer's key/value rows while
  * it reads them (the kept sets are final at once; the rows are final after
  * the next step, or as soon as a call that reads or writes rows, or plans
  * another event, moves them first).

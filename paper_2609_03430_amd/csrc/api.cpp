@@ -121,7 +121,8 @@ bool defers_moves(const ra_config& c) {
          c.policy != RA_POLICY_EXTERNAL && lists <= kMaxDropsBytes;
 }
 
-// Split arrival counters of the bf16 attention, one per (slot, KV head).
+// Split arrival counters of the attention, one per (slot, KV head), and the words
+// by which the split moves of an event order themselves.
 size_t arrivals_bytes(const ra_config& c) {
   return static_cast<size_t>(
       round_up(static_cast<int64_t>(sizeof(int32_t)) * c.max_seqs * c.num_kv_heads, 256));
@@ -179,7 +180,7 @@ struct ra_cache {
   std::vector<std::vector<int32_t>> groups;   // per slot: its table, in order
   // deferred row moves (see ra_end_step)
   int32_t* drops = nullptr;              // drop lists of the last events
-  int32_t* arrivals = nullptr;           // split arrival counters (bf16 attention)
+  int32_t* arrivals = nullptr;           // split arrival counters, event sync words
   // graph mode (see ra_graph_mode): launches that depend on no host state
   bool graph = false;
   Plan graph_plan;
@@ -288,7 +289,11 @@ void mirror_plan(SeqMeta& M, int r, bool at_trigger) {
 //   4 x 32 keys while a head has at most 12 workgroups: 8.9 at 1,090 keys
 //     (4 x 64: 9.7, 8 x 32: 11.5);
 //   4 x 64 keys beyond: 10.1 at 3,136 keys (4 x 32: 12.3, 25 partials per
-//     head to merge; 8 x 32: 11.7);
+//     head to merge; 8 x 32: 11.7).  From 13 to 17 workgroups either is within 7%
+//     (1,690 keys 10.4, with 4 x 32 9.7; 16 heads of 1,890 keys 10.3 and 10.9), from
+//     18 on 4 x 32 loses (2,690 keys 10.2 and 11.5; G = 1: 8.8 and 9.9; G = 8: 12.2
+//     and 14.8), at 10 and 11 it gains (1,290 keys 8.9 and 9.7, 7.5 and 8.1, 10.9 and
+//     11.7);
 //   past one workgroup per CU, 8 x 64: 16.3 at 16 heads of 5,000 keys (4 x 64:
 //     18.4) and 17.9 at 64 heads of 2,000 (18.8).
 // One wavefront per workgroup with 64 to 128 keys, merged by single

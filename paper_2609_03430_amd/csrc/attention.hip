@@ -9,8 +9,9 @@
 // query heads of the group and keeps an online softmax (running max and sum,
 // combined across lanes with wavefront shuffles); the W states merge in LDS.
 // A head with one split writes its normalised output directly; otherwise
-// every split writes an unnormalised partial and a small second kernel
-// merges them.  The step's new key/value is read from the input buffers by
+// every split writes an unnormalised partial, and the last one to finish
+// merges them (the contiguous 12-wavefront build: a second kernel).  The
+// step's new key/value is read from the input buffers by
 // the wavefront that owns the last key, which also stores it into the cache
 // after its reads, so no wavefront of the launch reads a row that is being
 // written.  Value tiles are read with nontemporal loads, key rows with
@@ -127,9 +128,7 @@ __device__ __forceinline__ void append_row(const Work& w, const SeqMeta* meta,
 //   ws_ml[((head * split_stride + split) * G + q) * 2 + {0,1}] = (m, l)
 // with m the running max of the scores in log2 units and l the sum of
 // 2^(s - m) over the split's keys.
-template <typename E>
-__global__ __launch_bounds__(256) void combine_kernel(AttnLaunch a, int G, int Hq, int Hkv,
-                                                      bool skip_single) {
+__global__ __launch_bounds__(256) void combine_kernel(AttnLaunch a, int G, int Hq, int Hkv) {
   __shared__ float sm[kMaxSplits * kMaxGroup];   // split maxima, then weights
   __shared__ float sl[kMaxSplits * kMaxGroup];   // split sums
   __shared__ float inv_l[kMaxGroup];
@@ -139,7 +138,7 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnLaunch a, int G, int H
   const int t = threadIdx.x;
   const int n_keys = M.len + 1;
   const int nsplit = (n_keys + a.split_keys - 1) / a.split_keys;
-  if (skip_single && nsplit == 1) return;
+  if (nsplit == 1) return;
   const int head = slot * Hkv + g;
   const float* ml = a.ws_ml + static_cast<int64_t>(head) * a.split_stride * G * 2;
   const float* po = a.ws_o + static_cast<int64_t>(head) * a.split_stride * G * kHeadDim;
@@ -161,7 +160,7 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnLaunch a, int G, int H
     inv_l[t] = 1.f / lsum;
   }
   __syncthreads();
-  E* out = static_cast<E*>(a.out);
+  uint16_t* out = static_cast<uint16_t*>(a.out);
   // one thread per (query, 4 channels)
   for (int item = t; item < G * (kHeadDim / 4); item += blockDim.x) {
     const int q = item / (kHeadDim / 4), c4 = (item % (kHeadDim / 4)) * 4;
@@ -175,10 +174,7 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnLaunch a, int G, int H
     acc *= inv_l[q];
     const int64_t orow = (static_cast<int64_t>(slot) * Hq + g * G + q) * kHeadDim + c4;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if constexpr (sizeof(E) == 2) out[orow + j] = f32_to_bf16(acc[j]);
-      else out[orow + j] = acc[j];
-    }
+    for (int j = 0; j < 4; ++j) out[orow + j] = f32_to_bf16(acc[j]);
   }
 }
 
@@ -190,10 +186,6 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnLaunch a, int G, int H
 __device__ __forceinline__ void store_shared_level(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ float load_shared_level(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 __device__ __forceinline__ void load_shared_level(const float* p, float& x, float& y) {
   const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
@@ -1245,8 +1237,7 @@ hipError_t launch_attention_t(const Shape& sh, const AttnLaunch& a, hipStream_t 
     // a head with several splits is merged by its last split (merge_if_last),
     // except in the contiguous 12-wavefront build
     if (a.max_splits > 1 && a.waves == 12 && !PAGED)
-      hipLaunchKernelGGL(combine_kernel<uint16_t>, cgrid, dim3(256), 0, s, a, sh.G, sh.Hq,
-                         sh.Hkv, true);
+      hipLaunchKernelGGL(combine_kernel, cgrid, dim3(256), 0, s, a, sh.G, sh.Hq, sh.Hkv);
   } else {
     if (a.waves != 4) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(attn_f32_kernel<PAGED>, grid, dim3(256), 0, s, a, sh.pg, sh.G, sh.Hq,

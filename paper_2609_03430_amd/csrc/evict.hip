@@ -639,10 +639,10 @@ __global__ __launch_bounds__(NT) void move_pending_kernel(
 // gets a workgroup of its own (grid: n_chunks per head of the listed slots),
 // which loads its source rows, says so, and writes once the workgroup of the
 // chunk before has loaded its own.  Rows move down by less than a chunk, so
-// those sources reach into this chunk, and no other chunk's do.  A head's workgroups
-// take their chunks in the order in which they start, so the one waited for
-// is always running or done, and it waits for nothing before it says so:
-// every wait ends.  A head's sync word counts the chunks taken (bits 0-4) and
+// those sources reach into this chunk, and no other chunk's do.  A head's
+// workgroups take their chunks in the order in which they start, so the one
+// waited for is always running or done, and it waits for nothing before it says
+// so: every wait ends.  A head's sync word counts the chunks taken (bits 0-4) and
 // the workgroups done (5-9) and has a bit per chunk loaded (10-30); the last
 // workgroup done clears it.
 //

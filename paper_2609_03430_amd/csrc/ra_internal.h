@@ -209,16 +209,17 @@ struct AttnLaunch {
   int max_seqs;
   int split_keys;
   int max_splits;
-  int waves;           // wavefronts per workgroup (bf16 path: 4, 8 or 12)
-  int short_runs;      // bf16, 8 wavefronts of at most 64 keys: the latency build
+  int waves;           // wavefronts per workgroup (bf16: 4, 8 or 12; fp32: 4)
+  int short_runs;      // bf16, 4 or 8 wavefronts of at most 64 keys: the latency build
   int wide_regs;       // bf16, 4 wavefronts: the build for one wavefront per SIMD
   // some sequence has a deferred row move (bf16, one split per head): the
   // launch runs the kernel that moves rows while it attends
   int move;
   const int32_t* drops;  // the deferred drop lists (see launch_evict)
   int drop_stride;
-  // bf16: per (slot, KV head) count of the splits done this launch, zero
-  // between launches (the last split resets it after merging)
+  // per (slot, KV head) count of the splits done this launch, zero between
+  // launches (the last split resets it after merging); the split moves of an
+  // event borrow the words (Shape::move_sync)
   int* arrivals;
 };
 hipError_t launch_attention(const Shape& sh, const AttnLaunch& a, hipStream_t s);

@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kNT, 2) void rkv_cbar_kernel(
     const SeqMeta* __restrict__ meta, const uint16_t* __restrict__ kpool,
     float* __restrict__ cbar_out, int stride, int n_heads, int n_chunks, int L, int Hkv, int r,
     int slot_lo, float threshold, int recent_dups) {
-  __shared__ uint16_t lk[2][kColBlk * kColStride];
+  __shared__ __align__(16) uint16_t lk[2][kColBlk * kColStride];   // 16-byte pieces
   __shared__ float linv[2][kColBlk];
   const int die = static_cast<int>(blockIdx.x) % kXcds, nth = static_cast<int>(blockIdx.x) / kXcds;
   const int head_idx = nth / n_chunks * kXcds + die;
