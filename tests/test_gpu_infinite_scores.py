@@ -26,11 +26,14 @@ CHRON, PAGED = B.RA_LAYOUT_CHRONOLOGICAL, B.RA_LAYOUT_PAGED
     (B.RA_BF16, 1, 8, 4, 1090, CHRON),       # nine workgroups of 4 x 32 keys
     (B.RA_BF16, 1, 2, 16, 6300, PAGED),      # 4 x 64 keys, 25 partials per head
     (B.RA_BF16, 4, 8, 2, 5000, CHRON),       # 8 x 64 keys
+    (B.RA_BF16, 25, 1, 16, 5190, CHRON),     # ten streamed items, several channel pairs a thread
+    (B.RA_BF16, 1, 1, 16, 1450, PAGED),      # twelve of 4 x 32 keys, the same
     (B.RA_BF16, 33, 8, 2, 3100, CHRON),      # halved heads
     (B.RA_BF16, 1, 8, 4, 40000, CHRON),      # 12 wavefronts, merged by a kernel of its own
     (B.RA_F32, 1, 2, 2, 130, CHRON),
     (B.RA_F32, 2, 8, 4, 1100, PAGED),
     (B.RA_F32, 40, 8, 1, 900, CHRON),
+    (B.RA_F32, 25, 1, 12, 9100, CHRON),      # ten items
     (B.RA_F32, 1, 1, 16, 9000, CHRON),
 ])
 def test_rows_of_infinite_scores(dtype, n, Hkv, G, rows, layout):
