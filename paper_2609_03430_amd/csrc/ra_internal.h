@@ -137,18 +137,21 @@ inline int event_chunks(const Shape& sh, int max_candidates) {
   const int chunk = event_chunk_rows(sh.dtype);
   // rows move down by less than a chunk: an event drops up to `every` rows
   if (heads > sh.move_words || sh.every + 8 > chunk) return 0;
-  // Two launches and the hand-over between the workgroups against one launch:
-  // the second chunk has to be most of one (microseconds per event of 8 to 32
-  // bf16 heads: 578 rows 25 to 26 in one launch, 28 to 30 split; 846: 28 to 30 and 29
-  // to 30; 996: 30 and 28 to 30; 1,296: 36 and 30 to 33; 9,100: 222 and 118), and more
-  // than 64 heads keep HBM busy by themselves: split, all their workgroups have to
-  // run at once, one to a CU (96 heads: 996 rows 37 and 36, 1,296 rows 45 and 50,
-  // 4,100 paged 136 and 140; 120 heads, 1,900 rows: 68 and 71; 64: 58 and 46).
-  // fp32 chunks are half as long and a head's take longer: 120 heads of 1,300 rows
-  // 93 and 88, of 1,050 80 and 83.
+  // Two launches and the hand-over between the workgroups against one launch
+  // (microseconds per event, one launch and split): the second chunk has to be
+  // most of one (8 to 64 bf16 heads, 64 drops: 560 rows 25 to 27 and 30 to 33, 840
+  // rows 30 to 33 and 30 to 34, 940 rows 32 to 35 and 29 to 34, 1,100 rows 37 to 41 and 31
+  // to 39; 9,100 rows 222 and 118 at 32 heads), and more than one where an event
+  // drops few rows, as a tile without a drop moves in fewer loads (16 drops: 940 rows
+  // 26 to 30 and 27 to 31, 1,100 rows 30 to 35 and 29 to 36); and more than 64 heads keep
+  // HBM busy by themselves: split, all their workgroups have to run at once, one to a
+  // CU (96 heads: 996 rows 37 and 36, 1,296 rows 45 and 50, 4,100 paged 136 and 140; 120
+  // heads, 1,900 rows: 68 and 71).  fp32 chunks are half as long and a head's take
+  // longer: 120 heads of 1,300 rows 93 and 88, of 1,050 80 and 83.
   const int64_t moved = static_cast<int64_t>(max_candidates) + sh.r;
   const int n = static_cast<int>((moved + 7 + chunk - 1) / chunk);
-  if (4 * moved <= 7 * chunk || n > kMaxChunks) return 0;
+  const int quarters = sh.dtype == 1 && sh.every < 48 ? 9 : 7;
+  if (4 * moved <= quarters * chunk || n > kMaxChunks) return 0;
   const bool few = heads <= 64 || heads * n <= 256;
   return few || (heads < 128 && sh.dtype == 0 && n >= 6) ? n : 0;
 }

@@ -2,9 +2,9 @@
 
 Sequences on their own eviction phases, so that an event concerns one or two
 of them; budgets whose moved rows are a little less, exactly and a little more
-than a whole number of chunks (512 rows of bf16, 256 of fp32), or than the 896
-rows from which bf16 moves split, and drop lists up to the longest that a chunk
-may have.  After every event the kept sets and
+than a whole number of chunks (512 rows of bf16, 256 of fp32), or than the 1,152
+(few drops) and 896 rows from which bf16 moves split, and drop lists up to the
+longest that a chunk may have.  After every event the kept sets and
 rows equal the oracle's, and the counters that order the moves are zero.
 """
 
@@ -19,12 +19,14 @@ pytestmark = pytest.mark.gpu
 # (dtype, layout, layers, KV heads, K, r, every, prompts)
 CASES = [
     (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 1, 2, 505, 0, 16, [3, 40]),
-    (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 1, 2, 890, 0, 16, [3, 40]),     # first event whole
+    (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 1, 2, 1140, 0, 16, [3, 40]),    # first event whole
+    (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 1, 2, 850, 0, 50, [3, 40]),
     (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 2, 2, 1024, 64, 64, [0, 17, 130]),
     (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 1, 4, 9000, 64, 64, [7, 1000]),
     (B.RA_BF16, B.RA_LAYOUT_CHRONOLOGICAL, 1, 1, 1500, 20, 500, [9, 100]),
     (B.RA_BF16, B.RA_LAYOUT_PAGED, 2, 2, 1100, 64, 64, [5, 90, 300]),
     (B.RA_BF16, B.RA_LAYOUT_PAGED, 1, 2, 961, 0, 32, [31, 64]),
+    (B.RA_BF16, B.RA_LAYOUT_PAGED, 1, 2, 960, 0, 64, [31, 64]),           # a third chunk for the alignment alone
     (B.RA_F32, B.RA_LAYOUT_CHRONOLOGICAL, 1, 2, 768, 8, 16, [1, 50]),
     (B.RA_F32, B.RA_LAYOUT_PAGED, 1, 2, 600, 64, 200, [10, 33]),
 ]

@@ -83,22 +83,24 @@ def test_lockstep_events_leave_their_moves_to_the_next_step(plans, n, prompt):
     assert [(x["move"], x["splits"]) for x in a] == [(0, halves), (1, 1), (0, halves)]
 
 
-@pytest.mark.parametrize("dtype,n,kv_heads,moved,layout,chunks", [
+@pytest.mark.parametrize("dtype,n,kv_heads,moved,every,layout,chunks", [
     # (moved: the candidates and recent rows of the event)
-    (B.RA_BF16, 1, 8, 578, CHRON, 0), (B.RA_BF16, 1, 8, 896, CHRON, 0),
-    (B.RA_BF16, 1, 8, 897, CHRON, 2), (B.RA_BF16, 1, 8, 1296, PAGED, 3),
-    (B.RA_BF16, 8, 8, 9000, PAGED, 18), (B.RA_BF16, 12, 8, 996, CHRON, 2),
-    (B.RA_BF16, 12, 8, 1296, CHRON, 0), (B.RA_BF16, 15, 8, 4000, PAGED, 0),
-    (B.RA_BF16, 1, 8, 10745, CHRON, 21), (B.RA_BF16, 1, 8, 10746, CHRON, 0),
-    (B.RA_F32, 1, 8, 396, CHRON, 0), (B.RA_F32, 1, 8, 449, PAGED, 2),
-    (B.RA_F32, 12, 8, 546, CHRON, 0), (B.RA_F32, 15, 8, 1050, CHRON, 0),
-    (B.RA_F32, 15, 8, 1300, CHRON, 6), (B.RA_F32, 16, 8, 1300, CHRON, 0),
+    (B.RA_BF16, 1, 8, 832, 64, CHRON, 0), (B.RA_BF16, 1, 8, 896, 64, PAGED, 0),
+    (B.RA_BF16, 1, 8, 960, 64, CHRON, 2), (B.RA_BF16, 1, 8, 1280, 64, PAGED, 3),
+    (B.RA_BF16, 1, 8, 1152, 1, CHRON, 0), (B.RA_BF16, 1, 8, 1153, 1, CHRON, 3),
+    (B.RA_BF16, 8, 8, 9000, 1, PAGED, 18), (B.RA_BF16, 12, 8, 960, 64, CHRON, 2),
+    (B.RA_BF16, 12, 8, 1280, 64, CHRON, 0), (B.RA_BF16, 15, 8, 4000, 1, PAGED, 0),
+    (B.RA_BF16, 1, 8, 10745, 1, CHRON, 21), (B.RA_BF16, 1, 8, 10746, 1, CHRON, 0),
+    (B.RA_F32, 1, 8, 448, 1, CHRON, 0), (B.RA_F32, 1, 8, 449, 1, PAGED, 2),
+    (B.RA_F32, 12, 8, 546, 1, CHRON, 0), (B.RA_F32, 15, 8, 1050, 1, CHRON, 0),
+    (B.RA_F32, 15, 8, 1300, 1, CHRON, 6), (B.RA_F32, 16, 8, 1300, 1, CHRON, 0),
 ])
-def test_events_split_where_the_second_launch_pays(plans, dtype, n, kv_heads, moved, layout,
+def test_events_split_where_the_second_launch_pays(plans, dtype, n, kv_heads, moved, every, layout,
                                                    chunks):
     """The moves of an event get workgroups of their own for a second chunk that
-    is most of one, and past 64 heads only while all of them run at once."""
-    a = plans([40] * n, dtype=dtype, layout=layout, kv_heads=kv_heads, budget=moved - 17, recent=16,
-              every=1, forward=moved - 1)[0]
-    assert a["evicted"] == n and a["len"] == 40 + moved - 1
+    is most of one (few drops: for a third), and past 64 heads only while all of
+    them run at once."""
+    a = plans([40] * n, dtype=dtype, layout=layout, kv_heads=kv_heads, budget=moved - 16 - every,
+              recent=16, every=every, forward=moved - 1)[0]
+    assert a["evicted"] == n and a["len"] == 40 + moved - every
     assert a["chunks"] == chunks
