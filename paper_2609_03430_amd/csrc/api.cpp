@@ -475,6 +475,10 @@ ra_status flush_pending(ra_cache* c, hipStream_t s) {
   return RA_OK;
 }
 
+// Rows that the 256 MB last-level cache still holds at an event, beside the step's
+// inputs and outputs.
+constexpr int64_t kCachedBytes = int64_t(192) << 20;
+
 // An event of the due slots of [lo, hi), listed in `list` unless they are too
 // many; deferred: positions and drop lists only.  The moves of a listed event
 // may share the attention's split counters, idle and zero between steps.
@@ -488,6 +492,10 @@ hipError_t launch_event(ra_cache* c, int lo, int hi, int candidates, bool deferr
     if (c->cfg.policy != RA_POLICY_EXTERNAL) {   // its rows pile up past evict_every
       sh.move_sync = reinterpret_cast<uint32_t*>(c->arrivals);
       sh.move_words = static_cast<int64_t>(c->cfg.max_seqs) * c->cfg.num_kv_heads;
+      int64_t rows = 0;
+      for (int i = c->slot_lo; i < c->slot_hi; ++i)
+        if (c->mirror[i].active) rows += c->mirror[i].len;
+      sh.cached = rows * heads * 2 * ra::kHeadDim * static_cast<int64_t>(c->elem) <= kCachedBytes;
     }
     return ra::launch_evict(sh, c->meta, c->kpool, c->vpool, c->pos, list.slot[0],
                             list.slot[0] + 1, candidates, deferred, s, drops, c->cfg.evict_every);

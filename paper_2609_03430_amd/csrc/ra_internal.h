@@ -82,6 +82,8 @@ struct Shape {
   // workgroups that share a head's move order themselves (evict.hip)
   uint32_t* move_sync = nullptr;
   int64_t move_words = 0;
+  // the active sequences' rows fit the last-level cache between two events
+  bool cached = false;
 };
 
 // Pool row of row j of one (sequence, layer, KV head) cache.
@@ -137,23 +139,26 @@ inline int event_chunks(const Shape& sh, int max_candidates) {
   const int chunk = event_chunk_rows(sh.dtype);
   // rows move down by less than a chunk: an event drops up to `every` rows
   if (heads > sh.move_words || sh.every + 8 > chunk) return 0;
-  // Two launches and the hand-over between the workgroups against one launch
-  // (microseconds per event, one launch and split): the second chunk has to be
-  // most of one (8 to 64 bf16 heads, 64 drops: 560 rows 25 to 27 and 30 to 33, 840
-  // rows 30 to 33 and 30 to 34, 940 rows 32 to 35 and 29 to 34, 1,100 rows 37 to 41 and 31
-  // to 39; 9,100 rows 222 and 118 at 32 heads), and more than one where an event
-  // drops few rows, as a tile without a drop moves in fewer loads (16 drops: 940 rows
-  // 26 to 30 and 27 to 31, 1,100 rows 30 to 35 and 29 to 36); and more than 64 heads keep
-  // HBM busy by themselves: split, all their workgroups have to run at once, one to a
-  // CU (96 heads: 996 rows 37 and 36, 1,296 rows 45 and 50, 4,100 paged 136 and 140; 120
-  // heads, 1,900 rows: 68 and 71).  fp32 chunks are half as long and a head's take
-  // longer: 120 heads of 1,300 rows 93 and 88, of 1,050 80 and 83.
+  // Two launches and the hand-over between the workgroups against one launch, in
+  // which one workgroup moves a head at 22 GB/s (microseconds per event, one launch
+  // and split, 8 to 64 bf16 heads): rows from HBM pay for the second from half of
+  // the second chunk on (700 rows 33 to 39 and 32 to 42, 760 rows 34 to 42 and 32 to 42,
+  // 900 rows 37 to 46 and 32 to 43, 1,100 rows 45 to 57 and 35 to 48; 4,000 rows, 32
+  // heads: 138 and 62), rows still in the last-level cache from most of it (64 drops: 840
+  // rows 30 to 37 and 30 to 40, 940 rows 32 to 40 and 29 to 41), or from the next one where
+  // an event drops few, as a tile without a drop moves in fewer loads (16 drops: 940
+  // rows 26 to 33 and 27 to 36, 1,100 rows 30 to 42 and 29 to 43).  More than 64 heads
+  // need all their workgroups at once, one to a CU, or moves long enough for several
+  // rounds of them (96 and 120 heads, from HBM: 960 rows 50 to 54 and 41 to 47, 1,100 rows
+  // 59 to 64 and 59 to 72, 1,900 rows 86 to 95 and 72 to 85; cached: 1,296 rows 45 to 56 and
+  // 50 to 62, 4,100 rows 127 to 143 and 125 to 164; fp32, cached: 1,300 rows 87 to 96 and 82 to
+  // 92).
   const int64_t moved = static_cast<int64_t>(max_candidates) + sh.r;
   const int n = static_cast<int>((moved + 7 + chunk - 1) / chunk);
-  const int quarters = sh.dtype == 1 && sh.every < 48 ? 9 : 7;
-  if (4 * moved <= quarters * chunk || n > kMaxChunks) return 0;
-  const bool few = heads <= 64 || heads * n <= 256;
-  return few || (heads < 128 && sh.dtype == 0 && n >= 6) ? n : 0;
+  const int quarters = sh.dtype == 0 ? 7 : !sh.cached ? 6 : sh.every < 48 ? 9 : 7;
+  if (4 * moved <= quarters * chunk || n > kMaxChunks || heads >= 128) return 0;
+  const int rounds_from = !sh.cached ? 4 : sh.dtype == 0 ? 6 : kMaxChunks + 1;
+  return heads <= 64 || heads * n <= 256 || n >= rounds_from ? n : 0;
 }
 // n_steps steps of the active slots of [lo, hi), positions only, events
 // included (the chronological layouts, a trigger period, and at most `rows`

@@ -3,8 +3,8 @@
 Sequences on their own eviction phases, so that an event concerns one or two
 of them; budgets whose moved rows are a little less, exactly and a little more
 than a whole number of chunks (512 rows of bf16, 256 of fp32), or than the 1,152
-(few drops) and 896 rows from which bf16 moves split, and drop lists up to the
-longest that a chunk may have.  After every event the kept sets and
+(few drops) and 896 rows from which bf16 moves of small caches split, and drop
+lists up to the longest that a chunk may have.  After every event the kept sets and
 rows equal the oracle's, and the counters that order the moves are zero.
 """
 

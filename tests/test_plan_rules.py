@@ -83,24 +83,30 @@ def test_lockstep_events_leave_their_moves_to_the_next_step(plans, n, prompt):
     assert [(x["move"], x["splits"]) for x in a] == [(0, halves), (1, 1), (0, halves)]
 
 
-@pytest.mark.parametrize("dtype,n,kv_heads,moved,every,layout,chunks", [
+@pytest.mark.parametrize("dtype,n,kv_heads,prompt,moved,every,layout,chunks", [
     # (moved: the candidates and recent rows of the event)
-    (B.RA_BF16, 1, 8, 832, 64, CHRON, 0), (B.RA_BF16, 1, 8, 896, 64, PAGED, 0),
-    (B.RA_BF16, 1, 8, 960, 64, CHRON, 2), (B.RA_BF16, 1, 8, 1280, 64, PAGED, 3),
-    (B.RA_BF16, 1, 8, 1152, 1, CHRON, 0), (B.RA_BF16, 1, 8, 1153, 1, CHRON, 3),
-    (B.RA_BF16, 8, 8, 9000, 1, PAGED, 18), (B.RA_BF16, 12, 8, 960, 64, CHRON, 2),
-    (B.RA_BF16, 12, 8, 1280, 64, CHRON, 0), (B.RA_BF16, 15, 8, 4000, 1, PAGED, 0),
-    (B.RA_BF16, 1, 8, 10745, 1, CHRON, 21), (B.RA_BF16, 1, 8, 10746, 1, CHRON, 0),
-    (B.RA_F32, 1, 8, 448, 1, CHRON, 0), (B.RA_F32, 1, 8, 449, 1, PAGED, 2),
-    (B.RA_F32, 12, 8, 546, 1, CHRON, 0), (B.RA_F32, 15, 8, 1050, 1, CHRON, 0),
-    (B.RA_F32, 15, 8, 1300, 1, CHRON, 6), (B.RA_F32, 16, 8, 1300, 1, CHRON, 0),
+    # every row in the last-level cache
+    (B.RA_BF16, 1, 8, 40, 832, 64, CHRON, 0), (B.RA_BF16, 1, 8, 40, 896, 64, PAGED, 0),
+    (B.RA_BF16, 1, 8, 40, 960, 64, CHRON, 2), (B.RA_BF16, 1, 8, 40, 1280, 64, PAGED, 3),
+    (B.RA_BF16, 1, 8, 40, 1152, 1, CHRON, 0), (B.RA_BF16, 1, 8, 40, 1153, 1, CHRON, 3),
+    (B.RA_BF16, 4, 8, 40, 9000, 1, PAGED, 18), (B.RA_BF16, 12, 8, 40, 960, 64, CHRON, 2),
+    (B.RA_BF16, 12, 8, 40, 1280, 64, CHRON, 0), (B.RA_BF16, 15, 8, 40, 3000, 1, PAGED, 0),
+    (B.RA_BF16, 1, 8, 40, 10745, 1, CHRON, 21), (B.RA_BF16, 1, 8, 40, 10746, 1, CHRON, 0),
+    (B.RA_F32, 1, 8, 40, 448, 1, CHRON, 0), (B.RA_F32, 1, 8, 40, 449, 1, PAGED, 2),
+    (B.RA_F32, 12, 8, 40, 546, 1, CHRON, 0), (B.RA_F32, 15, 8, 40, 1050, 1, CHRON, 0),
+    (B.RA_F32, 15, 8, 40, 1300, 1, CHRON, 6), (B.RA_F32, 16, 8, 40, 1300, 1, CHRON, 0),
+    # more rows than it holds
+    (B.RA_BF16, 8, 8, 6000, 768, 1, CHRON, 0), (B.RA_BF16, 8, 8, 6000, 769, 1, CHRON, 2),
+    (B.RA_BF16, 12, 8, 6000, 1018, 1, PAGED, 0), (B.RA_BF16, 15, 8, 6000, 1529, 1, CHRON, 0),
+    (B.RA_BF16, 15, 8, 6000, 1530, 1, CHRON, 4), (B.RA_BF16, 16, 8, 6000, 1530, 1, PAGED, 0),
+    (B.RA_F32, 15, 8, 6000, 761, 1, CHRON, 0), (B.RA_F32, 15, 8, 6000, 762, 1, CHRON, 4),
 ])
-def test_events_split_where_the_second_launch_pays(plans, dtype, n, kv_heads, moved, every, layout,
-                                                   chunks):
-    """The moves of an event get workgroups of their own for a second chunk that
-    is most of one (few drops: for a third), and past 64 heads only while all of
-    them run at once."""
-    a = plans([40] * n, dtype=dtype, layout=layout, kv_heads=kv_heads, budget=moved - 16 - every,
-              recent=16, every=every, forward=moved - 1)[0]
-    assert a["evicted"] == n and a["len"] == 40 + moved - every
+def test_events_split_where_the_second_launch_pays(plans, dtype, n, kv_heads, prompt, moved, every,
+                                                   layout, chunks):
+    """The moves of an event get workgroups of their own where the rows past the
+    first chunk pay for a second launch, and past 64 heads only while all of them
+    run at once or the moves are long."""
+    a = plans([prompt] * n, dtype=dtype, layout=layout, kv_heads=kv_heads,
+              budget=moved - 16 - every, recent=16, every=every, forward=moved - 1)[0]
+    assert a["evicted"] == n and a["len"] == prompt + moved - every
     assert a["chunks"] == chunks
