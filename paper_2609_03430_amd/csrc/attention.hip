@@ -214,7 +214,7 @@ struct Partial {
 // 8-byte loads all in flight together (4 or 16 splits per round trip), merged
 // by the thread itself with no exchange.  A thread with several items (more
 // channel pairs than threads) takes 5 to 12 splits without the four loads past
-// them (25 heads of 5,190 rows in 10 splits, G = 16: 27.5 -> 25.8 us).  Where the
+// them (25 heads of 5,190 rows in 10 splits, G = 16: 27.6 -> 25.4 us).  Where the
 // workgroup has more threads than the head has channel pairs, the splits are
 // dealt to `parts` groups of threads, which merge in LDS in split order.
 template <typename E, int NT>
@@ -275,10 +275,8 @@ __device__ void merge_if_last(const AttnLaunch& a, int G, int Hq, int Hkv) {
     return p;
   };
   const auto gather = [&](int item, int lo, int hi) {
-    const int n = hi - lo;
-    return n <= 4 ? gather_by(std::integral_constant<int, 4>{}, item, lo, hi)
-           : pairs > NT && n <= 12 ? gather_by(std::integral_constant<int, 12>{}, item, lo, hi)
-                                   : gather_by(std::integral_constant<int, 16>{}, item, lo, hi);
+    return hi - lo <= 4 ? gather_by(std::integral_constant<int, 4>{}, item, lo, hi)
+                        : gather_by(std::integral_constant<int, 16>{}, item, lo, hi);
   };
   const auto put = [&](int item, const Partial& p) {
     const float inv = 1.f / p.l;
@@ -289,6 +287,11 @@ __device__ void merge_if_last(const AttnLaunch& a, int G, int Hq, int Hkv) {
       *reinterpret_cast<float2*>(out + 2 * item) = make_float2(p.o0 * inv, p.o1 * inv);
     }
   };
+  if (pairs > NT && nsplit > 4 && nsplit <= 12) {
+    for (int item = t; item < pairs; item += NT)
+      put(item, gather_by(std::integral_constant<int, 12>{}, item, 0, nsplit));
+    return;
+  }
   if (parts == 1) {
     for (int item = t; item < pairs; item += NT) put(item, gather(item, 0, nsplit));
     return;
