@@ -329,8 +329,17 @@ void short_plan(Plan& p, int keys_max, int heads) {
 // 1,024 keys, 133 with 2,048; 384 heads of 2,000: 139 and 180 with one
 // workgroup per head), where they are few it only adds partials to merge (64
 // heads of 2,900: 40 us with 1,024 keys, 49 with 256).  Eight wavefronts to a
-// workgroup measured within 5%, mostly slower.
+// workgroup measured within 5%, mostly slower.  More heads than workgroups of four
+// fit the chip, two to a CU, of up to 64 keys: one wavefront each (one and four, us:
+// 800 heads of 31 keys, G = 1 17.4 and 19.1, G = 4 18.4 and 21.5; 2,400 heads 39 and 47,
+// 42 and 52; of 61 keys 49 and 54, 52 and 57; but 400 heads of 31 keys 13.9 and 12.3,
+// 15.0 and 13.5; of 71 keys alike).
 void plan_f32(Plan& p, int keys_max, int heads) {
+  if (keys_max <= 64 && heads > 512) {
+    p.group_waves = p.max_splits = 1;
+    p.split_keys = 64;
+    return;
+  }
   const int splits = std::max(1, (256 + heads / 2) / heads);
   int64_t keys = round_up((keys_max + splits - 1) / splits, 64);
   if (heads < 768) keys = std::min<int64_t>(keys, 1024);

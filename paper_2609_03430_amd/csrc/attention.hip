@@ -1106,18 +1106,18 @@ __device__ __forceinline__ void compute_block(Softmax& st, const BlockF32& b,
   }
 }
 
-// fp32 decode attention: a workgroup of four wavefronts per (sequence, KV
-// head, split), each streaming a quarter of the split's keys in 16-key blocks, two
+// fp32 decode attention: a workgroup of W wavefronts (four; one for many heads
+// of few keys, see plan_f32) per (sequence, KV
+// head, split), each streaming a W-th of the split's keys in 16-key blocks, two
 // blocks in flight.  Bound by HBM where the rows are many and by latency where
 // they are few; the group's queries are padded to 16, which the matrix cores
 // still do in a third of the time the rows take to arrive (64 products of 32
 // cycles per 16 KB block).  8 sequences of 8 heads, 2,900 rows: 40 us per
 // launch (4.7 TB/s) where single wavefronts on the vector ALU, one key per
 // lane, took 81 us (2.4 TB/s); 256 heads of 3,000 rows: 6.0 TB/s.
-template <bool PAGED>
-__global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnLaunch a, Paging pg, int G, int Hq,
-                                                          int Hkv, float scale_log2) {
-  constexpr int W = 4;
+template <int W, bool PAGED>
+__global__ __launch_bounds__(64 * W, 2) void attn_f32_kernel(AttnLaunch a, Paging pg, int G, int Hq,
+                                                             int Hkv, float scale_log2) {
   __shared__ float s_m[W][kMaxGroup];
   __shared__ float s_l[W][kMaxGroup];
   __shared__ float s_o[W][kMaxGroup][kHeadDim];
@@ -1246,9 +1246,14 @@ hipError_t launch_attention_t(const Shape& sh, const AttnLaunch& a, hipStream_t 
     if (a.max_splits > 1 && a.waves == 12 && !PAGED)
       hipLaunchKernelGGL(combine_kernel, cgrid, dim3(256), 0, s, a, sh.G, sh.Hq, sh.Hkv);
   } else {
-    if (a.waves != 4) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(attn_f32_kernel<PAGED>, grid, dim3(256), 0, s, a, sh.pg, sh.G, sh.Hq,
-                       sh.Hkv, scale_log2);
+    if (a.waves == 4)
+      hipLaunchKernelGGL((attn_f32_kernel<4, PAGED>), grid, dim3(256), 0, s, a, sh.pg, sh.G,
+                         sh.Hq, sh.Hkv, scale_log2);
+    else if (a.waves == 1)
+      hipLaunchKernelGGL((attn_f32_kernel<1, PAGED>), grid, dim3(64), 0, s, a, sh.pg, sh.G,
+                         sh.Hq, sh.Hkv, scale_log2);
+    else
+      return hipErrorInvalidConfiguration;
   }
   return hipGetLastError();
 }

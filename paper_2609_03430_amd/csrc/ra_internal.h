@@ -217,7 +217,7 @@ struct AttnLaunch {
   int max_seqs;
   int split_keys;
   int max_splits;
-  int waves;           // wavefronts per workgroup (bf16: 4, 8 or 12; fp32: 4)
+  int waves;           // wavefronts per workgroup (bf16: 4, 8 or 12; fp32: 4 or 1)
   int short_runs;      // bf16, 4 or 8 wavefronts of at most 64 keys: the latency build
   int wide_regs;       // bf16, 4 wavefronts: the build for one wavefront per SIMD
   // some sequence has a deferred row move (bf16, one split per head): the

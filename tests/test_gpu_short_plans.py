@@ -46,7 +46,8 @@ def test_short_plan(Hkv, G, lps, layout):
 # keys to many workgroups per head, an odd and an even number of blocks
 F32_CASES = [(1, 1, [0]), (2, 5, [14, 15, 16, 17]), (2, 2, [31, 47, 48, 63]), (1, 16, [64, 65]),
              (8, 4, [511, 512, 300]), (2, 3, [1039, 1055]), (4, 8, [2047, 2030] * 16),
-             (8, 2, [700, 32, 0] * 12), (8, 1, [130, 1025] * 50)]
+             (8, 2, [700, 32, 0] * 12), (8, 1, [130, 1025] * 50),
+             (8, 3, [0, 15, 16, 17, 31, 32, 62] * 10), (8, 16, [64, 0] * 33)]   # one wavefront, four
 
 
 @pytest.mark.parametrize("layout", [B.RA_LAYOUT_CHRONOLOGICAL, B.RA_LAYOUT_PAGED])

@@ -110,3 +110,11 @@ def test_events_split_where_the_second_launch_pays(plans, dtype, n, kv_heads, pr
               budget=moved - 16 - every, recent=16, every=every, forward=moved - 1)[0]
     assert a["evicted"] == n and a["len"] == prompt + moved - every
     assert a["chunks"] == chunks
+
+
+@pytest.mark.parametrize("n,keys,waves,splits", [
+    (65, 64, 1, 1), (65, 65, 4, 1), (64, 64, 4, 1), (300, 31, 1, 1),
+])
+def test_many_fp32_heads_of_few_keys_take_one_wavefront(plans, n, keys, waves, splits):
+    a = plans([keys - 1] * n, dtype=B.RA_F32)[0]
+    assert (a["waves"], a["splits"]) == (waves, splits)
